@@ -326,8 +326,7 @@ def workload_leg(name: str, seed: int, splits: int, flush, reps: int = 20) -> di
     out = torch.empty((w.B, w.Hq, w.d), dtype=torch.float16, device=dev)
     res = {"batch": w.B, "q_heads": w.Hq, "kv_heads": w.Hkv, "context": w.N, "window": w.n_tail,
            "k_sparsity": w.sK, "v_sparsity": w.sV,
-           # the library's routing: the matrix-core kernel from 8 query heads per kv-head
-           "kernel": "k_sparse_attn_mfma" if w.G >= 8 else "k_sparse_attn"}
+           "kernel": "k_sparse_attn_mfma"}
     # bulk prune + compress of the prefill (K and V), median of three
     Kp, Vp = K[:, :, :w.N].contiguous(), V[:, :, :w.N].contiguous()
     pc = []

@@ -270,24 +270,23 @@ enum mustafar_attn_kind {
     MUSTAFAR_ATTN_DENSE = 1
 };
 
-/* Split-K segment count a decode call of the given kind picks when it is
- * passed n_splits <= 0, for B*Hkv streams of n_tokens tokens (the compressed
- * tokens for the sparse calls). It depends on the kernel that runs: with one
- * query head per kv-head, many segments down to one 64-token block; with 2 or
- * 4 query heads per kv-head (the same bit walks), about 4096 workgroups of at
- * least 192 tokens; with 8 (the matrix-core kernel), about 2048 of at least
- * 128; the dense kernel with grouped queries about 4096 of at least 128.
- * With a route other than the default (mustafar_attn_set_route), the split
- * count follows the kernel the route picks. Returns 1 for invalid arguments
- * or kind. */
+/* Split-K segment count that a default-sized workspace provides for a decode call
+ * of the given kind over B*Hkv streams of n_tokens tokens (the compressed tokens
+ * for the sparse calls). One query head per kv-head: many segments down to one
+ * 64-token block; 2 or 4: about 4096 workgroups of at least 192 tokens; 8: about
+ * 2048 of at least 128; the dense kernel with grouped queries about 4096 of at
+ * least 128; a forced route (mustafar_attn_set_route) counts as 8 heads
+ * (MATRIX_CORES) or as 2 (WALKS). A call that is passed n_splits <= 0 takes this
+ * many segments on the walks and on the dense kernel; on the matrix-core kernel
+ * it takes what fills the GPU once, which is at most the larger of the two
+ * kinds' counts and never more than its workspace holds. Returns 1 for invalid
+ * arguments or kind. */
 int mustafar_attn_default_splits(int B, int Hq, int Hkv, int n_tokens, int kind);
 
-/* Kernel route of the sparse calls with grouped queries (2, 4 or 8 query heads
- * per kv-head; one head always takes the bit walks). DEFAULT: the bit walks
- * below 8 query heads per kv-head, the matrix-core kernel (zero-filled tiles
- * contracted with v_mfma) from 8 on, the faster of the two on MI355X at each
- * group size; WALKS and MATRIX_CORES force one kernel for every group size,
- * for comparing them. Both give the same results up to rounding (each within
+/* Kernel route of the sparse calls. DEFAULT: the matrix-core kernel (tiles
+ * expanded in registers, contracted with v_mfma), the faster one on MI355X at
+ * every group size; WALKS and MATRIX_CORES force one kernel for every group
+ * size, for comparing them. Both give the same results up to rounding (each within
  * the attention tolerance of the reference). The setting is process-wide and
  * takes effect for calls issued after it; it is not synchronized with calls
  * in flight on other threads. Errors: EINVAL (unknown route). */

@@ -7,6 +7,7 @@
 #include <atomic>
 #include <mutex>
 
+#include "attn_mfma.h"
 #include "mf_launch.h"
 #include "mustafar.h"
 
@@ -33,7 +34,7 @@ constexpr int kWalkTargetGroups = 32768;
 constexpr int kWalkMinSegTokens = 64;
 constexpr int kWalkGroupedTargetGroups = 4096;  // the walks with 2 or 4 query heads per kv-head,
 constexpr int kWalkGroupedMinSegTokens = 192;   // segments of at least 192 tokens
-constexpr int kMfmaMinGroup = 8;                // the matrix-core kernel from 8 on (attn_common.h)
+constexpr int kMfmaMinGroup = 8;                // 8 heads: the fewer, longer segments below
 constexpr int kMfmaTargetGroups = 2048;
 constexpr int kDenseGroupedTargetGroups = 4096;
 constexpr int kGroupedMinSegTokens = 128;
@@ -45,13 +46,19 @@ static_assert(MUSTAFAR_STREAM_POISONED == mf::kStreamPoisoned, "poisoned stream 
 // Kernel route of grouped queries (mustafar_attn_set_route), process-wide.
 std::atomic<int> g_route{MUSTAFAR_ROUTE_DEFAULT};
 
-// Whether a sparse call with G query heads per kv-head runs its compressed
-// segments on the matrix-core kernel.
-bool mfma_route(int G, int route) {
-  if (G < 2) return false;
-  if (route == MUSTAFAR_ROUTE_WALKS) return false;
-  if (route == MUSTAFAR_ROUTE_MATRIX_CORES) return true;
-  return G >= kMfmaMinGroup;
+// Whether a sparse call runs its compressed segments on the matrix-core kernel:
+// always, unless the walks are asked for. Matrix cores against walks, in us, on
+// one box (warm, best split of each): one head per kv-head 750 / 801 (512 streams
+// of 32K, K 50% V 70%) and 16.2 / 18.7 (32 streams of 4K, 50/50); two heads at
+// d = 64 16.4 / 20.7 (48 ragged streams of up to 9K); four 32.5 / 46.8 (32 of 16K,
+// 70/70) and 55 / 77 (8 of 128K); eight 34.3 / 70.
+bool mfma_route(int route) { return route != MUSTAFAR_ROUTE_WALKS; }
+
+// Split count of mustafar_attn_default_splits: 8 heads per kv-head or a forced
+// matrix-core route count the fewer, longer segments.
+bool long_segments(int G, int route) {
+  if (G < 2 || route == MUSTAFAR_ROUTE_WALKS) return false;
+  return route == MUSTAFAR_ROUTE_MATRIX_CORES || G >= kMfmaMinGroup;
 }
 
 bool aligned(const void* p, uintptr_t a) { return p && ((uintptr_t)p % a) == 0; }
@@ -450,7 +457,7 @@ int mustafar_attn_default_splits(int B, int Hq, int Hkv, int n_tokens, int kind)
   if (B < 1 || Hkv < 1 || Hq < Hkv || n_tokens < 1) return 1;
   if (kind != MUSTAFAR_ATTN_SPARSE && kind != MUSTAFAR_ATTN_DENSE) return 1;
   const bool grouped_q = Hq / Hkv >= 2;
-  const bool mfma = mfma_route(Hq / Hkv, g_route.load(std::memory_order_relaxed));
+  const bool mfma = long_segments(Hq / Hkv, g_route.load(std::memory_order_relaxed));
   const int64_t target = !grouped_q ? kWalkTargetGroups
                          : kind == MUSTAFAR_ATTN_DENSE ? kDenseGroupedTargetGroups
                          : mfma                        ? kMfmaTargetGroups
@@ -485,9 +492,34 @@ size_t mustafar_attn_workspace_bytes(int B, int Hq, int Hkv, int d, int n_tokens
   return (size_t)(rows * BHq * (int64_t)(d + 2) * (int64_t)sizeof(float) + BHq * (int64_t)sizeof(float));
 }
 
+// Segments of a sparse call that leaves the split to the library: one resident
+// round of waves (kMfmaCus CUs, `waves` each, one of them per stream for the
+// window), every wave taking the same number of 64-token blocks; where that makes
+// a segment of more than kMfmaLongTokens, as many rounds as bring it below.
+// Measured: 32 streams of 16K tokens (11 waves per CU) 32.5 us in one round (192
+// tokens) against 38 in one and a half (128) and 37 in 0.75 (256); 8 of 128K 55 us
+// in one round or two; 512 of 32K 750-759 us in segments of 1024 or 1344 tokens
+// against 771 (2048), 774 (512) and 860 (4096).
+constexpr int kMfmaCus = 256;
+constexpr int kMfmaLongTokens = 1024;
+static int mfma_splits(int64_t streams, int n_tokens, int waves) {
+  const int64_t round = (int64_t)kMfmaCus * waves;
+  const int64_t per_round = streams * n_tokens / round;  // tokens of a wave in one round
+  const int64_t rounds = per_round <= kMfmaLongTokens ? 1 : (per_round + kMfmaLongTokens - 1) / kMfmaLongTokens;
+  int64_t n = round * rounds / streams - 1;
+  if (n < 1) n = 1;
+  int64_t seg = ((int64_t)n_tokens / n + kSegAlign / 2) / kSegAlign * kSegAlign;  // the nearest whole blocks
+  if (seg < kSegAlign) seg = kSegAlign;
+  return (int)(((int64_t)n_tokens + seg - 1) / seg);
+}
+
+// K, V: the compressed caches of a sparse call, null for the dense one. On return
+// *splits is the split count that the workspace layout follows.
 static int decode_common(const void* q, int B, int Hq, int Hkv, int d, int n_s, int n_dense,
-                         int dense_is_window, int n_splits, float scale, void* out, void* ws,
-                         size_t ws_bytes, mf::AttnShape* sh, float** ws_ml, float** ws_o) {
+                         const mustafar_ccache_t* K, const mustafar_ccache_t* V, int n_splits, float scale,
+                         void* out, void* ws, size_t ws_bytes, mf::AttnShape* sh, float** ws_ml, float** ws_o,
+                         int* splits = nullptr) {
+  const bool dense_is_window = K != nullptr;
   if (B < 1 || Hq < 1 || Hkv < 1 || Hq % Hkv != 0) return MUSTAFAR_EINVAL;
   if ((int64_t)B * Hkv > kMaxGrid) return MUSTAFAR_EINVAL;
   if (!head_dim_ok(d)) return MUSTAFAR_EINVAL;
@@ -497,16 +529,27 @@ static int decode_common(const void* q, int B, int Hq, int Hkv, int d, int n_s, 
   const int G = Hq / Hkv;
   if (G != 1 && G != 2 && G != 4 && G != 8) return MUSTAFAR_EUNSUPPORTED;
   const int n_main = dense_is_window ? n_s : n_dense;
-  if (n_splits <= 0)
+  const bool mfma = dense_is_window && mfma_route(g_route.load(std::memory_order_relaxed));
+  const bool by_default = n_splits <= 0;
+  if (by_default)
     n_splits = mustafar_attn_default_splits(B, Hq, Hkv, n_main > 0 ? n_main : 1,
                                             dense_is_window ? MUSTAFAR_ATTN_SPARSE : MUSTAFAR_ATTN_DENSE);
   if (n_splits > (1 << 20)) return MUSTAFAR_EINVAL;
-  const size_t need = mustafar_attn_workspace_bytes(B, Hq, Hkv, d, n_main, n_splits);
-  if (!aligned(ws, 16) || ws_bytes < need) return MUSTAFAR_EWORKSPACE;
+  if (!aligned(ws, 16) || ws_bytes < mustafar_attn_workspace_bytes(B, Hq, Hkv, d, n_main, n_splits))
+    return MUSTAFAR_EWORKSPACE;
+  if (by_default && mfma && n_s > 0) {
+    // No more than a default-sized workspace holds, nor than this one does.
+    const int dn = mustafar_attn_default_splits(B, Hq, Hkv, n_s, MUSTAFAR_ATTN_DENSE);
+    const int most = dn > n_splits ? dn : n_splits;
+    int want = mfma_splits((int64_t)B * Hkv, n_s, mf::mfma_resident_waves(d / kTile, side_of(K), side_of(V)));
+    if (want > most) want = most;
+    if (ws_bytes >= mustafar_attn_workspace_bytes(B, Hq, Hkv, d, n_s, want)) n_splits = want;
+  }
+  if (splits) *splits = n_splits;
 
   sh->BHkv = B * Hkv;
   sh->G = G;
-  sh->mfma = dense_is_window && mfma_route(G, g_route.load(std::memory_order_relaxed));
+  sh->mfma = mfma;
   sh->T = d / kTile;
   sh->n_s = n_s;
   sh->n_dense = n_dense;
@@ -544,7 +587,7 @@ int mustafar_sparse_decode_attn(const void* q, int B, int Hq, const mustafar_cca
   if (n_tail > 0 && (!aligned(k_tail, 16) || !aligned(v_tail, 16))) return MUSTAFAR_EINVAL;
   mf::AttnShape sh;
   float *ws_ml, *ws_o;
-  st = decode_common(q, B, Hq, Kc->H, Kc->d, Kc->n_tokens, n_tail, 1, n_splits, scale, out, ws,
+  st = decode_common(q, B, Hq, Kc->H, Kc->d, Kc->n_tokens, n_tail, Kc, Vc, n_splits, scale, out, ws,
                      ws_bytes, &sh, &ws_ml, &ws_o);
   if (st != MUSTAFAR_OK) return st;
   return status_of(mf::launch_attention(sh, (const uint16_t*)q, side_of(Kc), side_of(Vc),
@@ -568,10 +611,10 @@ int mustafar_sparse_decode_attn_static(const void* q, int B, int Hq, const musta
   const int G = Hq / Kc->H;
   if (G != 1 && G != 2 && G != 4 && G != 8) return MUSTAFAR_EUNSUPPORTED;
   const int n_main = Kc->n_tokens;
-  if (n_splits <= 0)
-    n_splits = mustafar_attn_default_splits(B, Hq, Kc->H, n_main > 0 ? n_main : 1, MUSTAFAR_ATTN_SPARSE);
-  if (n_splits > (1 << 20)) return MUSTAFAR_EINVAL;
-  const size_t need = mustafar_attn_workspace_bytes(B, Hq, Kc->H, Kc->d, n_main, n_splits);
+  const int counted = n_splits > 0 ? n_splits
+                                   : mustafar_attn_default_splits(B, Hq, Kc->H, n_main > 0 ? n_main : 1, MUSTAFAR_ATTN_SPARSE);
+  if (counted > (1 << 20)) return MUSTAFAR_EINVAL;
+  const size_t need = mustafar_attn_workspace_bytes(B, Hq, Kc->H, Kc->d, n_main, counted);
   if (need > (size_t)MUSTAFAR_STATIC_SCRATCH_BYTES) return MUSTAFAR_ESCRATCH;
   void* ws = nullptr;
   if ((st = scratch_of_current_device(&ws)) != MUSTAFAR_OK) return st;
@@ -585,8 +628,8 @@ int mustafar_dense_decode_attn(const void* q, int B, int Hq, int Hkv, const void
   if (n_tokens < 1 || !aligned(k, 16) || !aligned(v, 16)) return MUSTAFAR_EINVAL;
   mf::AttnShape sh;
   float *ws_ml, *ws_o;
-  int st = decode_common(q, B, Hq, Hkv, d, 0, n_tokens, 0, n_splits, scale, out, ws, ws_bytes, &sh,
-                         &ws_ml, &ws_o);
+  int st = decode_common(q, B, Hq, Hkv, d, 0, n_tokens, nullptr, nullptr, n_splits, scale, out, ws, ws_bytes,
+                         &sh, &ws_ml, &ws_o);
   if (st != MUSTAFAR_OK) return st;
   mf::SparseSide none = {nullptr, nullptr, nullptr, nullptr, 0, 1, 0};
   return status_of(mf::launch_attention(sh, (const uint16_t*)q, none, none, (const uint16_t*)k,
@@ -729,7 +772,7 @@ int mustafar_window_decode_attn(const void* q, int B, int Hq, const mustafar_cca
   if (Kc->n_tokens != Vc->n_tokens) return MUSTAFAR_EINVAL;
   mf::AttnShape sh;
   float *ws_ml, *ws_o;
-  st = decode_common(q, B, Hq, Kc->H, Kc->d, Kc->n_tokens, w->W, 1, n_splits, scale, out, ws,
+  st = decode_common(q, B, Hq, Kc->H, Kc->d, Kc->n_tokens, w->W, Kc, Vc, n_splits, scale, out, ws,
                      ws_bytes, &sh, &ws_ml, &ws_o);
   if (st != MUSTAFAR_OK) return st;
   sh.n_comp = w->n_comp;
@@ -752,13 +795,11 @@ int mustafar_window_decode_attn_scores(const void* q, int B, int Hq, const musta
   if (active && !aligned(active, 4)) return MUSTAFAR_EINVAL;
   mf::AttnShape sh;
   float *ws_ml, *ws_o;
-  st = decode_common(q, B, Hq, Kc->H, Kc->d, Kc->n_tokens, w->W, 1, n_splits, scale, out, ws,
-                     ws_bytes, &sh, &ws_ml, &ws_o);
+  int splits = 0;
+  st = decode_common(q, B, Hq, Kc->H, Kc->d, Kc->n_tokens, w->W, Kc, Vc, n_splits, scale, out, ws,
+                     ws_bytes, &sh, &ws_ml, &ws_o, &splits);
   if (st != MUSTAFAR_OK) return st;
-  if (n_splits <= 0)
-    n_splits = mustafar_attn_default_splits(B, Hq, Kc->H, Kc->n_tokens > 0 ? Kc->n_tokens : 1,
-                                            MUSTAFAR_ATTN_SPARSE);
-  const size_t need = mustafar_attn_workspace_bytes(B, Hq, Kc->H, Kc->d, Kc->n_tokens, n_splits);
+  const size_t need = mustafar_attn_workspace_bytes(B, Hq, Kc->H, Kc->d, Kc->n_tokens, splits);
   float* lse2 = (float*)((char*)ws + need) - (int64_t)B * Hq;
   sh.n_comp = w->n_comp;
   sh.win_len = w->len;

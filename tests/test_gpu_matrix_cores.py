@@ -1,0 +1,64 @@
+"""The matrix-core attention kernel at the edges of its blocks and staging.
+
+A block is 64 / (d / 64) tokens in groups of 16; a key tile is staged in 16-byte
+pieces of 8 values and a block's values in chunks of 512, both bounded by the
+sparsity, which also picks the kernel's instance. The cases put the token count
+on either side of a group, a block and a segment, and the sparsity at all kept,
+each staging bound, a few values per token and none. Tolerance: the fp16 rounding
+of p (2^-11 relative) and of the output (2^-11 of max|o|), both below the 2e-3 of
+the other attention tests.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2505_22913_amd as mf
+from paper_2505_22913_amd import synth
+from tests.gpu_common import ATTN_TOL, announce, attn_error, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("sK,sV", [(0.0, 0.0), (0.0, 0.9), (0.35, 0.5), (0.7, 0.3), (0.7, 0.7), (0.97, 1.0), (1.0, 0.5)])
+def test_blocks_and_staging_bounds(d, sK, sV):
+    import torch
+    B, H = 1, 2
+    for n, G, splits in ((1, 1, 0), (15, 8, 0), (17, 4, 1), (32, 2, 1), (63, 1, 1), (65, 4, 1), (129, 1, 1), (200, 8, 2)):
+        announce(f"matrix cores d={d} s=({sK},{sV}) n={n} G={G} splits={splits}")
+        K, V = synth.make_kv(B, H, n, d, seed=n + d)
+        q = synth.make_q(B, H * G, d, seed=n)
+        Kc, Vc = mf.CompressedCache(B, H, d, sK, n), mf.CompressedCache(B, H, d, sV, n)
+        mf.mustafar_prune_compress(Kc, to_dev(K))
+        mf.mustafar_prune_compress(Vc, to_dev(V))
+        out = mf.mustafar_sparse_decode_attn(to_dev(q), Kc, Vc, n_splits=splits)
+        torch.cuda.synchronize()
+        ref = oracle.sparse_decode_attention(q, oracle.compress(K, sK), oracle.compress(V, sV),
+                                             np.zeros((B, H, 0, d), np.float16), np.zeros((B, H, 0, d), np.float16))
+        err = attn_error(out.cpu().numpy(), ref)
+        assert err <= ATTN_TOL, (n, G, err)
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+def test_full_tiles_beside_empty_ones(d):
+    # All kept channels of a token in one tile (the other tiles empty): the widest
+    # key tile and offsets that advance by whole tiles.
+    import torch
+    n, G = 70, 4
+    K, V = synth.make_kv(1, 1, n, d, seed=3)
+    for j in range(n):
+        lo = 64 * (j % (d // 64))
+        K[0, 0, j, lo:lo + 64] += np.float16(100) * np.sign(K[0, 0, j, lo:lo + 64])
+        V[0, 0, j, lo:lo + 64] += np.float16(100) * np.sign(V[0, 0, j, lo:lo + 64])
+    K *= np.float16(0.01)
+    q = synth.make_q(1, G, d, seed=5)
+    s = max(0.1, 1 - 64 / d)
+    Kc, Vc = mf.CompressedCache(1, 1, d, s, n), mf.CompressedCache(1, 1, d, s, n)
+    mf.mustafar_prune_compress(Kc, to_dev(K))
+    mf.mustafar_prune_compress(Vc, to_dev(V))
+    announce(f"matrix cores full tiles d={d}")
+    out = mf.mustafar_sparse_decode_attn(to_dev(q), Kc, Vc)
+    torch.cuda.synchronize()
+    ref = oracle.sparse_decode_attention(q, oracle.compress(K, s), oracle.compress(V, s),
+                                         np.zeros((1, 1, 0, d), np.float16), np.zeros((1, 1, 0, d), np.float16))
+    assert attn_error(out.cpu().numpy(), ref) <= ATTN_TOL
