@@ -777,45 +777,113 @@ __global__ __launch_bounds__(256) void k_query_lookahead(const uint16_t* __restr
   }
 }
 
-// The same weights for L = 32, 32 consecutive positions per thread: the thread
-// reads the |q| of the 63 positions its windows cover once (zeros past the
-// end, which leave an fp32 sum unchanged) and adds each into the windows that
-// contain it, position by position and query head by query head, so every
-// output gets exactly the additions, in the order, of the one-thread form.
-constexpr int kLookRun = 32;
+// The same weights for L = 32, a run of R consecutive positions per thread (R a
+// multiple of 32) and CPT channels. The |q| of a position goes into the 32 windows
+// that contain it, which the thread holds in registers: window k of a round of 32
+// positions starts at position k, so at position s the windows k <= s belong to
+// this round and the others to the last one; window (s + 1) % 32 is complete
+// after it. Position by position and query head by query head, so every output
+// gets exactly the additions, in the order, of the one-thread form (positions past
+// the end add zero, which leaves an fp32 sum unchanged). The first and the last
+// round add to the windows of the run only, so a run of R costs R x 32 additions
+// per head and channel. That is what bounds it: 2^33 additions (32 entries and
+// kv-heads of 16K positions, d = 128, 4 heads per kv-head) take 220 us at the VALU's
+// rate, the 805 MB of queries and weights 125 us. It takes 358 us; with runs of 32
+// positions and the 4 heads unrolled (5000 instructions a thread, 2-byte loads) it
+// took 1290. One head: 190 us. Loads one, three or four values ahead: the same.
+constexpr int kLookWin = 32;
 
-template <int G>
-__global__ __launch_bounds__(256) void k_query_lookahead32(const uint16_t* __restrict__ q, int B, int Hkv,
-                                                           int n_q, int d, float* __restrict__ w) {
-  constexpr int L = 32;
-  const int runs = (n_q + kLookRun - 1) / kLookRun;
-  const int64_t n = (int64_t)B * Hkv * runs * d;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int c = (int)(i % d);
-  const int run = (int)((i / d) % runs);
-  const int64_t bh = i / ((int64_t)d * runs);
-  const int b = (int)(bh / Hkv), h = (int)(bh % Hkv);
-  const int T0 = run * kLookRun;
-  const uint16_t* qb = q + ((int64_t)b * Hkv * G + (int64_t)h * G) * n_q * d + c;
-  float acc[kLookRun];
+template <int CPT>
+__device__ __forceinline__ void look_add(float (&acc)[CPT][kLookWin], int lo, int hi, uint32_t v) {
+  float a[CPT];
+  a[0] = half_bits_to_float((uint16_t)(v & 0x7fffu));
+  if constexpr (CPT == 2) a[1] = half_bits_to_float((uint16_t)((v >> 16) & 0x7fffu));
 #pragma unroll
-  for (int k = 0; k < kLookRun; ++k) acc[k] = 0.f;
+  for (int k = 0; k < kLookWin; ++k)
+    if (k >= lo && k < hi)
 #pragma unroll
-  for (int s = 0; s < kLookRun + L - 1; ++s) {
-    const int t = T0 + s;
+      for (int c = 0; c < CPT; ++c) acc[c][k] += a[c];
+}
+
+template <int CPT>
+__global__ __launch_bounds__(256) void k_query_lookahead32(const uint16_t* __restrict__ q, int64_t BHkv, int G,
+                                                           int n_q, int d, int R, float* __restrict__ w) {
+  const int cols = d / CPT;                     // a multiple of 64: waves stay in one run
+  const int runs = (n_q + R - 1) / R;
+  const int64_t wave = (int64_t)blockIdx.x * (256 / kWave) + threadIdx.x / kWave;
+  const int wpr = cols / kWave;                 // waves per run
+  if (wave >= BHkv * runs * wpr) return;
+  const int c = CPT * ((int)(wave % wpr) * kWave + (int)lane_id());
+  const int run = (int)((wave / wpr) % runs);
+  const int64_t bh = wave / ((int64_t)wpr * runs);
+  const int T0 = run * R, T1 = min(T0 + R, n_q);
+  const uint16_t* qb = q + bh * G * n_q * d + c;
+  float* wb = w + bh * n_q * d + c;
+  float acc[CPT][kLookWin];
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const float v = t < n_q ? fabsf(half_bits_to_float(qb[((int64_t)g * n_q + t) * d])) : 0.f;
+  for (int k = 0; k < kLookWin; ++k)
 #pragma unroll
-      for (int k = 0; k < kLookRun; ++k)
-        if (s >= k && s < k + L) acc[k] += v;   // window of output T0 + k: positions k .. k+L-1
+    for (int i = 0; i < CPT; ++i) acc[i][k] = 0.f;
+
+  // Values in additions order, each loaded kAhead of them ahead from src (head pg,
+  // position pt); past the end a load repeats the last position and counts as 0.
+  constexpr int kAhead = 2;
+  const int64_t head = (int64_t)n_q * d, back = d - (int64_t)(G - 1) * head;
+  const uint16_t* src = qb + (int64_t)T0 * d;
+  int pt = T0, pg = 0;
+  auto fetch = [&]() -> uint32_t {
+    uint32_t v;
+    if constexpr (CPT == 2) v = *reinterpret_cast<const uint32_t*>(src);
+    else v = *src;
+    const bool in = pt < n_q;
+    const bool wrap = ++pg == G;
+    if (wrap) {
+      pg = 0;
+      ++pt;
+    }
+    if (pt < n_q) src += wrap ? back : head;
+    return in ? v : 0u;
+  };
+  uint32_t ahead[kAhead];
+#pragma unroll
+  for (int i = 0; i < kAhead; ++i) ahead[i] = fetch();
+  auto next = [&]() {
+    const uint32_t v = ahead[0];
+#pragma unroll
+    for (int i = 0; i + 1 < kAhead; ++i) ahead[i] = ahead[i + 1];
+    ahead[kAhead - 1] = fetch();
+    return v;
+  };
+  auto emit = [&](int t, int k) {  // window k, which started at position t
+    if (t < T0 || t >= T1) return;
+    if constexpr (CPT == 2) *reinterpret_cast<float2*>(wb + (int64_t)t * d) = make_float2(acc[0][k], acc[1][k]);
+    else wb[(int64_t)t * d] = acc[0][k];
+  };
+
+  // Round 0: the windows that start in it.
+#pragma unroll
+  for (int s = 0; s < kLookWin; ++s)
+#pragma unroll 1
+    for (int g = 0; g < G; ++g) look_add<CPT>(acc, 0, s + 1, next());
+  emit(T0, 0);
+  const int rounds = (T1 - T0 + kLookWin - 1) / kLookWin;
+  for (int r = 1; r < rounds; ++r) {
+#pragma unroll
+    for (int s = 0; s < kLookWin; ++s) {
+#pragma unroll
+      for (int i = 0; i < CPT; ++i) acc[i][s] = 0.f;   // emitted at the position before
+#pragma unroll 1
+      for (int g = 0; g < G; ++g) look_add<CPT>(acc, 0, kLookWin, next());
+      emit(T0 + r * kLookWin + s - (kLookWin - 1), (s + 1) % kLookWin);
     }
   }
-  float* wb = w + (bh * n_q + T0) * (int64_t)d + c;
+  // Last round: what is left of the windows of the one before.
 #pragma unroll
-  for (int k = 0; k < kLookRun; ++k)
-    if (T0 + k < n_q) wb[(int64_t)k * d] = acc[k];
+  for (int s = 0; s < kLookWin - 1; ++s) {
+#pragma unroll 1
+    for (int g = 0; g < G; ++g) look_add<CPT>(acc, s + 1, kLookWin, next());
+    emit(T0 + rounds * kLookWin + s - (kLookWin - 1), s + 1);
+  }
 }
 
 // Prune, compress and append one token (d fp16 at src) to stream bh as token
@@ -1305,17 +1373,19 @@ hipError_t launch_append_variant(const CacheView& c, const uint16_t* x, int tok0
 
 hipError_t launch_query_lookahead(const uint16_t* q, int B, int Hq, int Hkv, int n_q, int T, int L,
                                   float* w, hipStream_t s) {
-  const int G = Hq / Hkv;
-  if (L == 32 && (G == 1 || G == 2 || G == 4 || G == 8)) {
-    const int64_t n = (int64_t)B * Hkv * ((n_q + kLookRun - 1) / kLookRun) * kTile * T;
-    const dim3 grid((uint32_t)((n + 255) / 256));
-    const int d = kTile * T;
-    switch (G) {
-      case 1: hipLaunchKernelGGL(k_query_lookahead32<1>, grid, dim3(256), 0, s, q, B, Hkv, n_q, d, w); break;
-      case 2: hipLaunchKernelGGL(k_query_lookahead32<2>, grid, dim3(256), 0, s, q, B, Hkv, n_q, d, w); break;
-      case 4: hipLaunchKernelGGL(k_query_lookahead32<4>, grid, dim3(256), 0, s, q, B, Hkv, n_q, d, w); break;
-      default: hipLaunchKernelGGL(k_query_lookahead32<8>, grid, dim3(256), 0, s, q, B, Hkv, n_q, d, w); break;
-    }
+  if (L == kLookWin) {
+    // Runs as long as leave four waves per SIMD (4096), 32 to 256 positions: a run
+    // reads the 31 positions after it again.
+    const int64_t BHkv = (int64_t)B * Hkv;
+    const int wpr = T >= 2 ? T / 2 : 1;
+    int R = 256;
+    while (R > kLookWin && BHkv * wpr * ((n_q + R - 1) / R) < 4096) R /= 2;
+    const int64_t waves = BHkv * wpr * ((n_q + R - 1) / R);
+    const dim3 grid((uint32_t)((waves + 3) / 4));
+    if (T >= 2)
+      hipLaunchKernelGGL(k_query_lookahead32<2>, grid, dim3(256), 0, s, q, BHkv, Hq / Hkv, n_q, kTile * T, R, w);
+    else
+      hipLaunchKernelGGL(k_query_lookahead32<1>, grid, dim3(256), 0, s, q, BHkv, Hq / Hkv, n_q, kTile * T, R, w);
     return hipGetLastError();
   }
   const int64_t n = (int64_t)B * Hkv * n_q * kTile * T;
