@@ -157,7 +157,7 @@ size_t mustafar_compress_workspace_bytes(int B, int H, int n_new);
  * On success c->n_tokens += n_new. Errors: EINVAL (bad descriptor, n_new < 1,
  * misaligned x), ECAPACITY (n_tokens + n_new > cap_tokens), EWORKSPACE.
  *
- * Completion status. Each chunk of 64 tokens finds its place in the stream by
+ * Completion status. Each chunk of tokens finds its place in the stream by
  * waiting for the running totals of the chunks before it (a single-pass
  * scan). That wait is bounded (MUSTAFAR_LOOKBACK_POLLS reads; the chunks it
  * waits for are always already running, so the bound is a guard, never

@@ -123,20 +123,12 @@ __device__ __forceinline__ void load_token(const uint16_t* __restrict__ src, uin
 constexpr uint64_t kFlagAgg = 1ull << 62;     // the chunk's own total is known
 constexpr uint64_t kFlagPrefix = 2ull << 62;  // the stream offset after the chunk is known
 constexpr uint32_t kBadBase = 0xffffffffu;    // look_back gave up
+constexpr uint32_t kGaveUp = 0x80000000u;     // in a stream's count of decided chunks: one gave up
 
 __global__ void k_clear(uint32_t* __restrict__ p, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x)
     p[i] = 0u;
-}
-
-// After a bulk compression (stream-ordered, so every chunk has finished): a
-// stream one of whose chunks gave up has holes, so its stream_len becomes
-// kStreamPoisoned, which every later call treats as "skip this stream".
-__global__ void k_compress_finalize(const uint32_t* __restrict__ gave_up, uint32_t* __restrict__ stream_len,
-                                    int BH) {
-  const int bh = blockIdx.x * blockDim.x + threadIdx.x;
-  if (bh < BH && gave_up[bh] != 0u) stream_len[bh] = kStreamPoisoned;
 }
 
 // The flag words are the only data workgroups exchange (the count travels in
@@ -296,18 +288,15 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// compress_waves() waves per workgroup; a chunk is that many runs of 64 tokens
-// (32 from d = 128 on) of one stream, one run per wave. The waves select and
-// pack their runs side by side and share the chunk's ticket, scan total and
-// look-back, so those cost once per chunk (two waves: 4% off the bulk
-// compression of a 50% cache against one; four measured the same).
+// W waves per workgroup; a chunk is W runs of 64 tokens (32 from d = 128 on) of
+// one stream, one run per wave. The waves select and pack their runs side by side
+// and share the chunk's ticket, scan total and look-back, so those cost once per
+// chunk (two waves: 4% off the bulk compression of a 50% cache against one; which
+// W when: compress_launch).
 // PRESET: the keep-masks are the bitmaps already in the cache for these tokens
 // (a pruner variant selected them); only the scan and the packing run.
-template <int T>
-constexpr int compress_waves() { return 2; }
-
-template <int T, bool PRESET = false>
-__global__ __launch_bounds__(compress_waves<T>() * kWave) void k_compress(const uint16_t* __restrict__ x, int n_new, int k_all,
+template <int T, bool PRESET, int W>
+__global__ __launch_bounds__(W * kWave) void k_compress(const uint16_t* __restrict__ x, int n_new, int k_all,
                                                     uint64_t* __restrict__ bitmaps,
                                                     uint32_t* __restrict__ offsets,
                                                     uint16_t* __restrict__ values,
@@ -316,10 +305,10 @@ __global__ __launch_bounds__(compress_waves<T>() * kWave) void k_compress(const 
                                                     uint64_t* __restrict__ flags,
                                                     uint32_t* __restrict__ ticket_ctr, int n_chunks,
                                                     int64_t x_stride, PruneOpts o, uint32_t max_polls,
-                                                    uint32_t* __restrict__ gave_up,
+                                                    uint32_t* __restrict__ decided,
                                                     uint32_t* __restrict__ status) {
   constexpr int d = kTile * T;
-  constexpr int kCompressWaves = compress_waves<T>();
+  constexpr int kCompressWaves = W;
   constexpr int LPT = T >= 2 ? 2 : 1;      // lanes per token (selection and packing)
   constexpr int TPW = kWave / LPT;          // tokens per wave
   constexpr int CPL = d / LPT;              // channels per lane
@@ -550,20 +539,36 @@ __global__ __launch_bounds__(compress_waves<T>() * kWave) void k_compress(const 
     }
   }
 
+  // Chunks of the stream that were decided (their base found or given up) before
+  // this one, and whether one gave up.
+  uint32_t n_decided = 0u;
   if (wave == 0) {
     const uint32_t b = look_back(flags + (int64_t)bh * n_chunks, chunk, run, first, lane, max_polls, f0);
     if (lane == 0) s_share[kCompressWaves + 1] = b;
-    if (lane == 0 && b == kBadBase) {
-      // Mark the stream and the call; k_compress_finalize poisons the stream
-      // once every chunk has finished.
-      __hip_atomic_store(gave_up + bh, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane == 0) {
+      if (b == kBadBase) {
+        __hip_atomic_fetch_or(decided + bh, kGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      } else if (chunk == n_chunks - 1) {
+        __hip_atomic_store(stream_len + bh, b + run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __threadfence();  // before this chunk counts as decided
+      }
+      n_decided = __hip_atomic_fetch_add(decided + bh, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (lane == 0 && chunk == n_chunks - 1 && b != kBadBase) stream_len[bh] = b + run;
   }
   lds_barrier();  // the chunk's base
   const uint32_t base = __builtin_amdgcn_readfirstlane((int)s_share[kCompressWaves + 1]);
-  if (base == kBadBase) return;  // look-back gave up: nothing is written
+  // The last chunk to be decided poisons a stream with a hole: its length has been
+  // written by then, and every workgroup of it has read the old one. (The count
+  // arrives while the run is written.)
+  auto settle = [&]() {
+    if (threadIdx.x == 0 && (n_decided & kGaveUp) != 0u && (n_decided & ~kGaveUp) == (uint32_t)n_chunks - 1u)
+      __hip_atomic_store(stream_len + bh, kStreamPoisoned, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  if (base == kBadBase) {  // look-back gave up: nothing is written
+    settle();
+    return;
+  }
 
   // The wave's packed run (a multiple of 8 values, 16-byte aligned in the
   // stream), after the runs of the waves before it.
@@ -582,6 +587,7 @@ __global__ __launch_bounds__(compress_waves<T>() * kWave) void k_compress(const 
       offsets[tile0 + t] = base + wave_off + lane_off + tile_pos[t];
     }
   }
+  settle();
 }
 
 // Output-aware keep-mask of one token, lane = channel: the score |x| * w in
@@ -1216,26 +1222,41 @@ __global__ __launch_bounds__(256) void k_window_fill(WindowView w, int b, int d,
   }
 }
 
-// Clears the workspace, runs k_compress (PRESET: with the bitmaps already in the
-// cache) and poisons the streams one of whose chunks gave up.
+// Clears the workspace and runs k_compress (PRESET: with the bitmaps already in the
+// cache).
 template <int T, bool PRESET>
 static hipError_t compress_launch(const CacheView& c, const uint16_t* x, int n_new, int64_t x_stride,
                                   int tok0, uint32_t* ws, hipStream_t s, const PruneOpts& o,
                                   uint32_t max_polls) {
-  const int n_chunks = (n_new + compress_chunk_tokens(T) - 1) / compress_chunk_tokens(T);
+  // Waves per workgroup, i.e. the chunk. A chunk's base needs the totals of all
+  // chunks before it, and few streams have many chunks of each in flight that wait
+  // for one another: with two waves, 32 streams of 16K tokens at d = 128 (50%) took
+  // 110 us against 60 with eight, 8 of 128K 295 against 163 (139 with 16, which
+  // leaves one workgroup a CU and costs 10-20% from 32 streams on), 128 of 16K 217
+  // against 172; 512 streams the same. d = 256: four (60 against 76; eight 68). A
+  // caller's bound on the look-back counts chunks of two waves.
+  const int W = max_polls != kLookbackPolls ? 2 : T == 4 ? 4 : c.BH <= 16 ? 16 : 8;
+  const int chunk = compress_chunk_tokens(T) / 2 * W;
+  const int n_chunks = (n_new + chunk - 1) / chunk;
   const int64_t n_wg = (int64_t)c.BH * n_chunks;
   const CompressWs w = compress_ws(ws, c.BH, n_chunks);
   const int clear_blocks = (int)((w.words + 255) / 256 < 1024 ? (w.words + 255) / 256 : 1024);
   hipLaunchKernelGGL(k_clear, dim3(clear_blocks), dim3(256), 0, s, ws, w.words);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_compress<T, PRESET>), dim3((uint32_t)n_wg), dim3(compress_waves<T>() * kWave),
-                     0, s, x, n_new, PRESET ? 0 : c.n_keep,
-                     c.bitmaps, c.offsets, c.values, c.stream_len, c.cap_tokens, tok0, c.val_stride,
-                     w.flags, w.ticket, n_chunks, x_stride, o, max_polls, w.bad, w.status);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_compress_finalize, dim3((c.BH + 255) / 256), dim3(256), 0, s, w.bad, c.stream_len,
-                     c.BH);
+  auto launch = [&](auto kernel, int waves) {
+    hipLaunchKernelGGL(kernel, dim3((uint32_t)n_wg), dim3(waves * kWave), 0, s, x, n_new, PRESET ? 0 : c.n_keep,
+                       c.bitmaps, c.offsets, c.values, c.stream_len, c.cap_tokens, tok0, c.val_stride,
+                       w.flags, w.ticket, n_chunks, x_stride, o, max_polls, w.decided, w.status);
+  };
+  if constexpr (T == 4) {
+    if (W == 4) launch(k_compress<T, PRESET, 4>, 4);
+    else launch(k_compress<T, PRESET, 2>, 2);
+  } else {
+    if (W == 16) launch(k_compress<T, PRESET, 16>, 16);
+    else if (W == 8) launch(k_compress<T, PRESET, 8>, 8);
+    else launch(k_compress<T, PRESET, 2>, 2);
+  }
   return hipGetLastError();
 }
 

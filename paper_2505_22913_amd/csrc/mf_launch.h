@@ -6,8 +6,8 @@
 
 namespace mf {
 
-// Tokens per two-wave workgroup of the bulk compression (one lane per token at
-// d = 64, two lanes per token from d = 128 on).
+// Tokens per two waves of the bulk compression (one lane per token at d = 64, two
+// lanes per token from d = 128 on), its smallest workgroup.
 constexpr int compress_chunk_tokens(int T) { return T >= 2 ? 64 : 128; }
 // Smallest chunk over the supported head sizes, for workspace sizing.
 constexpr int kMinCompressChunk = 64;
@@ -34,12 +34,13 @@ constexpr uint32_t kLookbackPolls = 1u << 20;
 
 // Workspace of the bulk compression: a u32 status word at byte 0 (nonzero once a
 // stream gave up; 16 bytes reserved), then u64 look-back flags [BH][n_chunks],
-// u32 ticket counters [BH] and u32 give-up marks [BH]. Cleared by each call.
+// u32 ticket counters [BH] and u32 counts of decided chunks [BH] (with the give-up
+// mark). Cleared by each call.
 struct CompressWs {
   uint32_t* status;
   uint64_t* flags;
   uint32_t* ticket;
-  uint32_t* bad;
+  uint32_t* decided;
   int64_t words;  // 32-bit words to clear from ws
 };
 inline CompressWs compress_ws(uint32_t* ws, int64_t BH, int64_t n_chunks) {
@@ -47,7 +48,7 @@ inline CompressWs compress_ws(uint32_t* ws, int64_t BH, int64_t n_chunks) {
   w.status = ws;
   w.flags = reinterpret_cast<uint64_t*>(ws + 4);
   w.ticket = reinterpret_cast<uint32_t*>(w.flags + BH * n_chunks);
-  w.bad = w.ticket + BH;
+  w.decided = w.ticket + BH;
   w.words = 4 + 2 * BH * n_chunks + 2 * BH;
   return w;
 }
