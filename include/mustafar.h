@@ -392,7 +392,7 @@ int mustafar_window_init(mustafar_window_t* w, void* k, void* v, void* len, void
  * fill window slots 0.. in order; len[b], head[b] = 0 and n_comp[b] are set.
  * Afterwards Kc/Vc->n_tokens and w->max_len hold the batch maxima. ws: at
  * least mustafar_compress_workspace_bytes(1, H, n_max) bytes, 8-byte aligned
- * (used by one entry after the other). With a per-channel Vc (the grouped
+ * (more, up to that of all B entries, lets more entries share a launch). With a per-channel Vc (the grouped
  * lifecycle, see mustafar_window_step_grouped) the compressed prefix is instead
  * the first 32 * floor((seq_len[b] - 1) / 32) tokens, whole groups, values
  * pruned per channel by magnitude. Errors: EINVAL, ECAPACITY, EWORKSPACE. */

@@ -474,7 +474,7 @@ def mustafar_window_prefill(win: DenseWindow, Kc: CompressedCache, Vc: Compresse
     import torch
     n_max = int(x_k.shape[2])
     lens = (ctypes.c_int32 * len(seq_len))(*[int(n) for n in seq_len])
-    need = mustafar_compress_workspace_bytes(1, win.desc.H, max(n_max, 1))
+    need = mustafar_compress_workspace_bytes(win.desc.B, win.desc.H, max(n_max, 1))  # every entry at once
     if ws is None:
         ws = torch.empty(max(need, 16), dtype=torch.uint8, device=x_k.device)
     _check("mustafar_window_prefill", lib().mustafar_window_prefill(

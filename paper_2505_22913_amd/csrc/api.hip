@@ -194,8 +194,8 @@ int prefill_window_len(const mustafar_window_t* w, const mustafar_ccache_t* Vc, 
   return n < w->W ? n : w->W;
 }
 
-// The streams of batch entry b as a one-entry cache (same buffers).
-mustafar_ccache_t entry_view(const mustafar_ccache_t* c, int b) {
+// The streams of batch entries b .. b + n - 1 as a cache of its own (same buffers).
+mustafar_ccache_t entry_view(const mustafar_ccache_t* c, int b, int n) {
   mustafar_ccache_t v = *c;
   const int64_t s0 = (int64_t)b * c->H;
   const int64_t tiles = s0 * c->cap_tokens * (c->d / kTile);
@@ -203,7 +203,7 @@ mustafar_ccache_t entry_view(const mustafar_ccache_t* c, int b) {
   v.offsets = c->offsets + tiles;
   v.values = c->values + s0 * c->val_stride;
   v.stream_len = c->stream_len + s0;
-  v.B = 1;
+  v.B = n;
   v.n_tokens = 0;
   return v;
 }
@@ -679,24 +679,41 @@ int mustafar_window_prefill(mustafar_window_t* w, mustafar_ccache_t* Kc, mustafa
     return MUSTAFAR_EWORKSPACE;
   const hipStream_t s = (hipStream_t)stream;
   const int64_t entry = (int64_t)w->H * n_max * w->d;  // fp16 elements per batch entry of x
-  for (int b = 0; b < w->B; ++b) {
-    const int len = prefill_window_len(w, Vc, seq_len[b]);
-    const int n_comp = seq_len[b] - len;
-    const uint16_t* xk = (const uint16_t*)x_k + b * entry;
-    const uint16_t* xv = (const uint16_t*)x_v + b * entry;
-    if (n_comp > 0) {
-      const mustafar_ccache_t kb = entry_view(Kc, b), vb = entry_view(Vc, b);
-      const hipError_t ev =
-          grouped(Vc) ? mf::launch_compress_channel(view_of(&vb), xv, n_comp, 0, (uint32_t*)ws, s, nullptr, n_max)
-                      : mf::launch_compress(view_of(&vb), xv, n_comp, 0, (uint32_t*)ws, s, n_max);
-      if ((st = status_of(mf::launch_compress(view_of(&kb), xk, n_comp, 0, (uint32_t*)ws, s, n_max))) !=
+  // As many entries at a time as the workspace has look-back flags for: one call's
+  // worth for a single entry is enough for several, as a chunk of many streams is
+  // longer than the one it is sized by. (One entry at a time took 4 to 6 launches
+  // each: 48 for 8 entries, of 4 to 9 us.)
+  for (int b0 = 0; b0 < w->B;) {
+    int n = w->B - b0 < mf::kMaxPruneHeads ? w->B - b0 : mf::kMaxPruneHeads;
+    while (max_comp > 0 && n > 1 && mf::compress_ws_bytes(w->d / kTile, (int64_t)n * w->H, n_max) > ws_bytes) n = (n + 1) / 2;
+    int32_t comp[mf::kMaxPruneHeads], len[mf::kMaxPruneHeads];
+    int most_comp = 0, most_len = 0;
+    for (int e = 0; e < n; ++e) {
+      len[e] = prefill_window_len(w, Vc, seq_len[b0 + e]);
+      comp[e] = seq_len[b0 + e] - len[e];
+      if (comp[e] > most_comp) most_comp = comp[e];
+      if (len[e] > most_len) most_len = len[e];
+    }
+    const uint16_t* xk = (const uint16_t*)x_k + b0 * entry;
+    const uint16_t* xv = (const uint16_t*)x_v + b0 * entry;
+    if (most_comp > 0) {
+      const mustafar_ccache_t kb = entry_view(Kc, b0, n), vb = entry_view(Vc, b0, n);
+      mf::CacheView kv = view_of(&kb), vv = view_of(&vb);
+      kv.entry_streams = vv.entry_streams = w->H;
+      kv.entry_tokens = vv.entry_tokens = comp;
+      if ((st = status_of(grouped(Vc) ? mf::launch_compress_channel(vv, xv, most_comp, 0, (uint32_t*)ws, s, nullptr, n_max)
+                                      : mf::launch_compress(vv, xv, most_comp, 0, (uint32_t*)ws, s, n_max))) !=
               MUSTAFAR_OK ||
-          (st = status_of(ev)) != MUSTAFAR_OK)
+          (st = status_of(mf::launch_compress(kv, xk, most_comp, 0, (uint32_t*)ws, s, n_max))) != MUSTAFAR_OK)
         return st;
     }
-    if ((st = status_of(mf::launch_window_fill(window_view_of(w), b, w->d, xk, xv, n_max, n_comp, len,
-                                               s))) != MUSTAFAR_OK)
+    mf::WindowView wv = window_view_of(w);
+    wv.fill_entries = n;
+    wv.fill_first = comp;
+    wv.fill_count = len;
+    if ((st = status_of(mf::launch_window_fill(wv, b0, w->d, xk, xv, n_max, most_comp, most_len, s))) != MUSTAFAR_OK)
       return st;
+    b0 += n;
   }
   Kc->n_tokens = max_comp;
   Vc->n_tokens = max_comp;

@@ -324,6 +324,11 @@ __global__ __launch_bounds__(W * kWave) void k_compress(const uint16_t* __restri
   // Workgroups take the streams in turn and, within a stream, ordered tickets
   // from the stream's counter (one counter per stream keeps the atomics spread).
   const int bh = (int)(blockIdx.x % (gridDim.x / (uint32_t)n_chunks));
+  // This stream's tokens and chunks (n_new and n_chunks are the largest).
+  const int n_mine = o.per_entry ? o.head_keep[bh / o.H] : n_new;
+  const int own_chunks = (n_mine + W * TPW - 1) / (W * TPW);
+  const int guess = (int)(blockIdx.x / (gridDim.x / (uint32_t)n_chunks));
+  if (guess >= own_chunks) return;
   // A stream poisoned by an earlier call takes no more tokens: every workgroup
   // of it leaves before drawing a ticket (the last chunk, which rewrites
   // stream_len, draws the last ticket, after every other workgroup's read).
@@ -336,8 +341,8 @@ __global__ __launch_bounds__(W * kWave) void k_compress(const uint16_t* __restri
   auto stage_load = [&](int ch, u32x4_t (&r)[kIt]) {
     const int sj0 = ch * kChunk + wave * TPW;
     const u32x4_t* src = reinterpret_cast<const u32x4_t*>(
-        x + ((int64_t)bh * x_stride + (sj0 < n_new ? sj0 : ch * kChunk)) * d);
-    const int n16 = max(min(TPW, n_new - sj0), 0) * P16;
+        x + ((int64_t)bh * x_stride + (sj0 < n_mine ? sj0 : ch * kChunk)) * d);
+    const int n16 = max(min(TPW, n_mine - sj0), 0) * P16;
 #pragma unroll
     for (int i = 0; i < kIt; ++i) {
       const int c = i * kWave + (int)lane;
@@ -349,7 +354,6 @@ __global__ __launch_bounds__(W * kWave) void k_compress(const uint16_t* __restri
   // the rare case that the ticket differs). The ticket is drawn with an
   // increment: the wave-aggregating rewrite of an add waits for its result
   // at once.
-  const int guess = (int)(blockIdx.x / (gridDim.x / (uint32_t)n_chunks));
   uint32_t tk = 0u;
   if (threadIdx.x == 0) tk = atomicInc(ticket_ctr + bh, 0xffffffffu);
   u32x4_t r[kIt];
@@ -361,7 +365,7 @@ __global__ __launch_bounds__(W * kWave) void k_compress(const uint16_t* __restri
   const int k = o.per_head ? o.head_keep[bh % o.H] : k_all;  // kept channels of this stream
   const int jc = chunk * kChunk;                // the chunk's first token
   const int j0 = jc + wave * TPW;               // this wave's first token
-  const int nt = min(TPW, n_new - j0);          // <= 0: the chunk ends before this wave's half
+  const int nt = min(TPW, n_mine - j0);          // <= 0: the chunk ends before this wave's half
   const uint32_t base_lds = (uint32_t)(uintptr_t)s_rows;
   {
     const int n16 = max(nt, 0) * P16;
@@ -390,7 +394,7 @@ __global__ __launch_bounds__(W * kWave) void k_compress(const uint16_t* __restri
   uint32_t keep[NW];
   if constexpr (PRESET) {
     // (a wave whose run lies past the chunk's end reads nothing: its tokens
-    // are past n_new, possibly past the cache's capacity)
+    // are past the stream's, possibly past the cache's capacity)
     const int jt = min((int)lane / LPT, max(nt, 1) - 1);
     const int64_t tb = ((int64_t)bh * cap_tokens + tok0 + j0 + jt) * T + ((int)lane % LPT) * (T / LPT);
 #pragma unroll
@@ -549,7 +553,7 @@ __global__ __launch_bounds__(W * kWave) void k_compress(const uint16_t* __restri
       if (b == kBadBase) {
         __hip_atomic_fetch_or(decided + bh, kGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      } else if (chunk == n_chunks - 1) {
+      } else if (chunk == own_chunks - 1) {
         __hip_atomic_store(stream_len + bh, b + run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __threadfence();  // before this chunk counts as decided
       }
@@ -562,7 +566,7 @@ __global__ __launch_bounds__(W * kWave) void k_compress(const uint16_t* __restri
   // written by then, and every workgroup of it has read the old one. (The count
   // arrives while the run is written.)
   auto settle = [&]() {
-    if (threadIdx.x == 0 && (n_decided & kGaveUp) != 0u && (n_decided & ~kGaveUp) == (uint32_t)n_chunks - 1u)
+    if (threadIdx.x == 0 && (n_decided & kGaveUp) != 0u && (n_decided & ~kGaveUp) == (uint32_t)own_chunks - 1u)
       __hip_atomic_store(stream_len + bh, kStreamPoisoned, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
   if (base == kBadBase) {  // look-back gave up: nothing is written
@@ -736,13 +740,14 @@ __device__ __forceinline__ void group_bitmaps(const uint32_t (&word)[T], uint32_
 template <int T, bool SCORED>
 __global__ __launch_bounds__(256) void k_select_channel(CacheView c, const uint16_t* __restrict__ x,
                                                         int n_new, int64_t x_stride, int tok0,
-                                                        const float* __restrict__ w) {
+                                                        const float* __restrict__ w, PruneOpts o) {
   constexpr int d = kTile * T;
   constexpr int R = (kGroup * T + kWave - 1) / kWave;
   const int groups = n_new / kGroup;
   const int64_t wave = (int64_t)blockIdx.x * (256 / kWave) + threadIdx.x / kWave;
   if (wave >= (int64_t)c.BH * groups) return;
   const int bh = (int)(wave / groups), g = (int)(wave % groups);
+  if (o.per_entry && g >= o.head_keep[bh / o.H] / kGroup) return;
   const uint32_t lane = lane_id();
   const int64_t row0 = (int64_t)bh * x_stride + (int64_t)g * kGroup;
   uint32_t word[T];
@@ -1199,26 +1204,35 @@ __global__ void k_window_commit_grouped(WindowView w, const int32_t* __restrict_
   }
 }
 
-// Prefill of one batch entry's window: tokens [first, first + count) of each of
-// its H streams (x: [H][x_stride][d]) into ring slots 0.., and its state.
+// Prefill of the windows of batch entries b .. b + gridDim.y - 1: tokens
+// [first, first + count) of each of an entry's H streams (x: the first entry's
+// [H][x_stride][d], entries one after the other) into ring slots 0.., and its
+// state. 16 bytes a thread (rows are 128 bytes or more, 16-byte aligned).
+struct FillSpans {
+  int32_t first[kMaxPruneHeads], count[kMaxPruneHeads];
+};
+
 __global__ __launch_bounds__(256) void k_window_fill(WindowView w, int b, int d,
                                                      const uint16_t* __restrict__ xk,
                                                      const uint16_t* __restrict__ xv,
-                                                     int64_t x_stride, int first, int count) {
-  const int64_t per_stream = (int64_t)count * d;
+                                                     int64_t x_stride, FillSpans spans) {
+  const int e = blockIdx.y, first = spans.first[e], count = spans.count[e];
+  const int64_t row = d / 8, per_stream = count * row;   // 16-byte pieces
   const int64_t n = (int64_t)w.H * per_stream;
+  const u32x4_t* sk = reinterpret_cast<const u32x4_t*>(xk) + (int64_t)e * w.H * x_stride * row;
+  const u32x4_t* sv = reinterpret_cast<const u32x4_t*>(xv) + (int64_t)e * w.H * x_stride * row;
+  u32x4_t* dk = reinterpret_cast<u32x4_t*>(w.k) + (int64_t)(b + e) * w.H * w.W * row;
+  u32x4_t* dv = reinterpret_cast<u32x4_t*>(w.v) + (int64_t)(b + e) * w.H * w.W * row;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
     const int64_t h = i / per_stream, r = i % per_stream;
-    const int64_t dst = ((int64_t)b * w.H + h) * w.W * d + r;
-    const int64_t src = (h * x_stride + first) * d + r;
-    w.k[dst] = xk[src];
-    w.v[dst] = xv[src];
+    dk[h * w.W * row + r] = sk[(h * x_stride + first) * row + r];
+    dv[h * w.W * row + r] = sv[(h * x_stride + first) * row + r];
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    w.len[b] = count;
-    w.head[b] = 0;
-    w.n_comp[b] = first;
+    w.len[b + e] = count;
+    w.head[b + e] = 0;
+    w.n_comp[b + e] = first;
   }
 }
 
@@ -1228,14 +1242,7 @@ template <int T, bool PRESET>
 static hipError_t compress_launch(const CacheView& c, const uint16_t* x, int n_new, int64_t x_stride,
                                   int tok0, uint32_t* ws, hipStream_t s, const PruneOpts& o,
                                   uint32_t max_polls) {
-  // Waves per workgroup, i.e. the chunk. A chunk's base needs the totals of all
-  // chunks before it, and few streams have many chunks of each in flight that wait
-  // for one another: with two waves, 32 streams of 16K tokens at d = 128 (50%) took
-  // 110 us against 60 with eight, 8 of 128K 295 against 163 (139 with 16, which
-  // leaves one workgroup a CU and costs 10-20% from 32 streams on), 128 of 16K 217
-  // against 172; 512 streams the same. d = 256: four (60 against 76; eight 68). A
-  // caller's bound on the look-back counts chunks of two waves.
-  const int W = max_polls != kLookbackPolls ? 2 : T == 4 ? 4 : c.BH <= 16 ? 16 : 8;
+  const int W = compress_waves(T, c.BH, max_polls != kLookbackPolls);
   const int chunk = compress_chunk_tokens(T) / 2 * W;
   const int n_chunks = (n_new + chunk - 1) / chunk;
   const int64_t n_wg = (int64_t)c.BH * n_chunks;
@@ -1267,6 +1274,17 @@ static hipError_t compress_T(const CacheView& c, const uint16_t* x, int n_new, i
   return compress_launch<T, false>(c, x, n_new, x_stride, tok0, ws, s, o, max_polls);
 }
 
+// Options of a launch that compresses another number of tokens for each entry.
+static PruneOpts entry_opts(const CacheView& c) {
+  PruneOpts o;
+  if (c.entry_tokens != nullptr) {
+    o.per_entry = 1;
+    o.H = c.entry_streams;
+    for (int b = 0; b < c.BH / c.entry_streams; ++b) o.head_keep[b] = c.entry_tokens[b];
+  }
+  return o;
+}
+
 template <int T>
 static hipError_t append_T(const CacheView& c, const uint16_t* x, int tok0, hipStream_t s) {
   dim3 grid((c.BH + 3) / 4);
@@ -1294,9 +1312,9 @@ hipError_t launch_compress(const CacheView& c, const uint16_t* x, int n_new, int
                            hipStream_t s, int64_t x_stride, uint32_t max_polls) {
   if (x_stride <= 0) x_stride = n_new;
   switch (c.T) {
-    case 1: return compress_T<1>(c, x, n_new, x_stride, tok0, ws, s, PruneOpts{}, max_polls);
-    case 2: return compress_T<2>(c, x, n_new, x_stride, tok0, ws, s, PruneOpts{}, max_polls);
-    case 4: return compress_T<4>(c, x, n_new, x_stride, tok0, ws, s, PruneOpts{}, max_polls);
+    case 1: return compress_T<1>(c, x, n_new, x_stride, tok0, ws, s, entry_opts(c), max_polls);
+    case 2: return compress_T<2>(c, x, n_new, x_stride, tok0, ws, s, entry_opts(c), max_polls);
+    case 4: return compress_T<4>(c, x, n_new, x_stride, tok0, ws, s, entry_opts(c), max_polls);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1326,7 +1344,7 @@ hipError_t launch_append_kv(const CacheView& kc, const CacheView& vc, const uint
 template <int T>
 static hipError_t pack_preset_T(const CacheView& c, const uint16_t* x, int n_new, int64_t x_stride,
                                 int tok0, uint32_t* ws, hipStream_t s, uint32_t max_polls = kLookbackPolls) {
-  return compress_launch<T, true>(c, x, n_new, x_stride, tok0, ws, s, PruneOpts{}, max_polls);
+  return compress_launch<T, true>(c, x, n_new, x_stride, tok0, ws, s, entry_opts(c), max_polls);
 }
 
 template <int T>
@@ -1336,9 +1354,11 @@ static hipError_t compress_channel_T(const CacheView& c, const uint16_t* x, int 
   const int64_t waves = (int64_t)c.BH * (n_new / kGroup);
   const dim3 grid((uint32_t)((waves + 3) / 4));
   if (w != nullptr)
-    hipLaunchKernelGGL((k_select_channel<T, true>), grid, dim3(256), 0, s, c, x, n_new, x_stride, tok0, w);
+    hipLaunchKernelGGL((k_select_channel<T, true>), grid, dim3(256), 0, s, c, x, n_new, x_stride, tok0, w,
+                       entry_opts(c));
   else
-    hipLaunchKernelGGL((k_select_channel<T, false>), grid, dim3(256), 0, s, c, x, n_new, x_stride, tok0, w);
+    hipLaunchKernelGGL((k_select_channel<T, false>), grid, dim3(256), 0, s, c, x, n_new, x_stride, tok0, w,
+                       entry_opts(c));
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return pack_preset_T<T>(c, x, n_new, x_stride, tok0, ws, s, max_polls);
@@ -1419,11 +1439,16 @@ hipError_t launch_query_lookahead(const uint16_t* q, int B, int Hq, int Hkv, int
 hipError_t launch_window_fill(const WindowView& w, int b, int d, const uint16_t* xk,
                               const uint16_t* xv, int64_t x_stride, int first, int count,
                               hipStream_t s) {
-  const int64_t n = (int64_t)w.H * count * d;
+  const int entries = w.fill_entries > 0 ? w.fill_entries : 1;
+  FillSpans spans;
+  for (int e = 0; e < entries; ++e) {
+    spans.first[e] = w.fill_entries > 0 ? w.fill_first[e] : first;
+    spans.count[e] = w.fill_entries > 0 ? w.fill_count[e] : count;
+  }
+  const int64_t n = (int64_t)w.H * count * d / 8;
   int blocks = (int)((n + 255) / 256);
   blocks = blocks < 1 ? 1 : (blocks > 1024 ? 1024 : blocks);
-  hipLaunchKernelGGL(k_window_fill, dim3(blocks), dim3(256), 0, s, w, b, d, xk, xv, x_stride, first,
-                     count);
+  hipLaunchKernelGGL(k_window_fill, dim3(blocks, entries), dim3(256), 0, s, w, b, d, xk, xv, x_stride, spans);
   return hipGetLastError();
 }
 

@@ -23,7 +23,24 @@ struct CacheView {
   int cap_tokens;    // token capacity per stream
   int64_t val_stride;
   int group_keep;    // per-channel caches: tokens kept per channel and group of 32; else -1
+  // Host only, for launch_compress and launch_compress_channel: the tokens to
+  // compress of each batch entry (entry_streams streams each, at most
+  // kMaxPruneHeads entries); n_new is then the largest of them.
+  int entry_streams = 0;
+  const int32_t* entry_tokens = nullptr;
 };
+
+// Waves per workgroup of the bulk compression of BH streams, i.e. its chunk. A
+// chunk's base needs the totals of all chunks before it, and few streams have
+// many chunks of each in flight that wait for one another: with two waves, 32
+// streams of 16K tokens at d = 128 (50%) took 110 us against 60 with eight, 8 of
+// 128K 295 against 163 (139 with 16, which leaves one workgroup a CU and costs
+// 10-20% from 32 streams on), 128 of 16K 217 against 172; 512 streams the same.
+// d = 256: four (60 against 76; eight 68). A caller's bound on the look-back
+// counts chunks of two waves.
+constexpr int compress_waves(int T, int64_t BH, bool bounded) {
+  return bounded ? 2 : T == 4 ? 4 : BH <= 16 ? 16 : 8;
+}
 
 // A stream whose bulk compression gave up waiting in the look-back (see
 // k_compress) has this stream_len; every later call skips it.
@@ -43,14 +60,20 @@ struct CompressWs {
   uint32_t* decided;
   int64_t words;  // 32-bit words to clear from ws
 };
+inline int64_t compress_ws_words(int64_t BH, int64_t n_chunks) { return 4 + 2 * BH * n_chunks + 2 * BH; }
 inline CompressWs compress_ws(uint32_t* ws, int64_t BH, int64_t n_chunks) {
   CompressWs w;
   w.status = ws;
   w.flags = reinterpret_cast<uint64_t*>(ws + 4);
   w.ticket = reinterpret_cast<uint32_t*>(w.flags + BH * n_chunks);
   w.decided = w.ticket + BH;
-  w.words = 4 + 2 * BH * n_chunks + 2 * BH;
+  w.words = compress_ws_words(BH, n_chunks);
   return w;
+}
+
+inline size_t compress_ws_bytes(int T, int64_t BH, int64_t n_new) {
+  const int64_t chunk = compress_chunk_tokens(T) / 2 * compress_waves(T, BH, false);
+  return 4u * (size_t)compress_ws_words(BH, (n_new + chunk - 1) / chunk);
 }
 
 // Compress n_new tokens per stream (x: [BH][x_stride][64T] fp16, x_stride = n_new
@@ -73,6 +96,7 @@ struct PruneOpts {
   int mode = 0;
   int H = 1;                  // kv-heads: stream s is head s % H
   int per_head = 0;           // head_keep holds each head's kept count
+  int per_entry = 0;          // head_keep holds the tokens to compress of each batch entry (H streams)
   const float* weights = nullptr;  // output-aware: fp32 [BH][x_stride][64T] channel weights
   int32_t head_keep[kMaxPruneHeads] = {};
 };
@@ -103,6 +127,11 @@ struct WindowView {
   int32_t* head;
   int32_t* n_comp;
   int B, H, W;
+  // Host only, for launch_window_fill: the first token and the tokens of entries
+  // b .. b + fill_entries - 1 (at most kMaxPruneHeads); count is then the largest.
+  int fill_entries = 0;
+  const int32_t* fill_first = nullptr;
+  const int32_t* fill_count = nullptr;
 };
 hipError_t launch_window_fill(const WindowView& w, int b, int d, const uint16_t* xk,
                               const uint16_t* xv, int64_t x_stride, int first, int count,
