@@ -293,9 +293,16 @@ __device__ __forceinline__ void lds_barrier() {
 // and share the chunk's ticket, scan total and look-back, so those cost once per
 // chunk (two waves: 4% off the bulk compression of a 50% cache against one; which
 // W when: compress_launch).
-// PRESET: the keep-masks are the bitmaps already in the cache for these tokens
-// (a pruner variant selected them); only the scan and the packing run.
-template <int T, bool PRESET, int W>
+// MODE kPreset: the keep-masks are the bitmaps already in the cache for these tokens
+// (a pruner variant selected them); only the scan and the packing run. MODE
+// kScored: output-aware selection, the same bit-sliced search over the 31 bits of
+// the fp32 scores |x| w (o.weights). What bounds that mode is the reading of the
+// weights (twice the bytes of the tokens): 32 streams of 16K tokens at d = 128
+// (70%) take 119 us, where a kernel that counted the ballots of one token a wave
+// (250 scalar instructions a token) and the packing after it took 258. MODE
+// kTwoFour: the two largest of every four channels; 66 us at 50% (146 with the ballots).
+enum { kMagnitude = 0, kPreset = 1, kScored = 2, kTwoFour = 3 };
+template <int T, int MODE, int W>
 __global__ __launch_bounds__(W * kWave) void k_compress(const uint16_t* __restrict__ x, int n_new, int k_all,
                                                     uint64_t* __restrict__ bitmaps,
                                                     uint32_t* __restrict__ offsets,
@@ -392,7 +399,7 @@ __global__ __launch_bounds__(W * kWave) void k_compress(const uint16_t* __restri
   // Keep-mask of this lane's token: NW words of 32 channels, channel order.
   constexpr int NW = NR / 16;
   uint32_t keep[NW];
-  if constexpr (PRESET) {
+  if constexpr (MODE == kPreset) {
     // (a wave whose run lies past the chunk's end reads nothing: its tokens
     // are past the stream's, possibly past the cache's capacity)
     const int jt = min((int)lane / LPT, max(nt, 1) - 1);
@@ -403,24 +410,94 @@ __global__ __launch_bounds__(W * kWave) void k_compress(const uint16_t* __restri
       keep[2 * t] = (uint32_t)bm;
       keep[2 * t + 1] = (uint32_t)(bm >> 32);
     }
+  } else if constexpr (MODE == kTwoFour) {
+    // Keys of a quad made distinct (magnitude, then the lower channel); those from
+    // the second largest on are kept.
+#pragma unroll
+    for (int g = 0; g < NW; ++g) {
+      uint32_t word = 0u;
+#pragma unroll
+      for (int m = 7; m >= 0; --m) {
+        const uint32_t p0 = raw[16 * g + 2 * m], p1 = raw[16 * g + 2 * m + 1];
+        const uint32_t key[4] = {(p0 & 0x7fffu) << 2 | 3u, (p0 >> 14 & 0x1fffcu) | 2u, (p1 & 0x7fffu) << 2 | 1u,
+                                 p1 >> 14 & 0x1fffcu};
+        const uint32_t hi0 = max(key[0], key[1]), lo0 = min(key[0], key[1]);
+        const uint32_t hi1 = max(key[2], key[3]), lo1 = min(key[2], key[3]);
+        const uint32_t second = max(min(hi0, hi1), max(lo0, lo1));
+#pragma unroll
+        for (int i = 3; i >= 0; --i) word = word << 1 | (key[i] >= second ? 1u : 0u);
+      }
+      keep[g] = word;
+    }
   } else {
     // Register 16 g + i holds the keys of channels 32 g + i (low half) and
     // 32 g + 16 + i (high half), so that bit r of plane word b of group g is
     // bit b of channel 32 g + r: the planes come out in channel order. The
     // sign bits land in plane 15, which the search never reads.
-    uint32_t pl[NR];
+    constexpr int NP = MODE == kScored ? 32 : 16;  // bit planes, the sign's included
+    uint32_t pl[NW * NP];                          // pl[NP g + b] = plane b of group g
+    if constexpr (MODE == kScored) {
+      // The weights of a group of 32 channels of every lane, through the wave's rows
+      // in LDS (its tokens are in registers by now): 16-byte pieces, 8 lanes a
+      // token's half, rows padded like the tokens'.
+      constexpr int WROW = LPT * 128 + 16;
+      static_assert(WROW <= ROW, "weight rows fit the token rows");
+      const float* wsrc = o.weights + ((int64_t)bh * x_stride + (nt > 0 ? j0 : jc)) * d;
+      auto weight_load = [&](int g, u32x4_t (&r)[8]) {
 #pragma unroll
-    for (int g = 0; g < NW; ++g) {
-      uint32_t r[16];
+        for (int i = 0; i < 8; ++i) {
+          const int seg = i * 8 + (int)lane / 8;
+          const int tok = min(seg / LPT, max(nt, 1) - 1);
+          r[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(wsrc + (int64_t)tok * d + (seg % LPT) * CPL + 32 * g) + lane % 8);
+        }
+      };
+      u32x4_t wr[8];
+      weight_load(0, wr);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const uint32_t a = raw[16 * g + j], b = raw[16 * g + 8 + j];
-        r[2 * j] = __builtin_amdgcn_perm(b, a, 0x05040100u);      // low halves of a and b
-        r[2 * j + 1] = __builtin_amdgcn_perm(b, a, 0x07060302u);  // high halves
+      for (int g = 0; g < NW; ++g) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int seg = i * 8 + (int)lane / 8;
+          *reinterpret_cast<u32x4_t*>(s_rows + (seg / LPT) * WROW + (seg % LPT) * 128 + (lane % 8) * 16) = wr[i];
+        }
+        if (g + 1 < NW) weight_load(g + 1, wr);
+        uint32_t key[32];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const u32x4_t v = *reinterpret_cast<const u32x4_t*>(s_rows + ((int)lane / LPT) * WROW + ((int)lane % LPT) * 128 + 16 * i);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int c = 4 * i + e;
+            const uint32_t pair = raw[16 * g + c / 2];
+            const float m = half_bits_to_float((uint16_t)((c & 1 ? pair >> 16 : pair) & 0x7fffu));
+            key[c] = __float_as_uint(m * __uint_as_float(v[e]));
+          }
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          uint32_t r[16];
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            r[i] = __builtin_amdgcn_perm(key[16 + i], key[i], h ? 0x07060302u : 0x05040100u);
+          transpose16x2(r);
+#pragma unroll
+          for (int i = 0; i < 16; ++i) pl[NP * g + 16 * h + i] = r[i];
+        }
       }
-      transpose16x2(r);
+    } else {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) pl[16 * g + i] = r[i];  // pl[16g + b] = plane b of group g
+      for (int g = 0; g < NW; ++g) {
+        uint32_t r[16];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const uint32_t a = raw[16 * g + j], b = raw[16 * g + 8 + j];
+          r[2 * j] = __builtin_amdgcn_perm(b, a, 0x05040100u);      // low halves of a and b
+          r[2 * j + 1] = __builtin_amdgcn_perm(b, a, 0x07060302u);  // high halves
+        }
+        transpose16x2(r);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) pl[16 * g + i] = r[i];
+      }
     }
     uint32_t cand[NW], above[NW];
 #pragma unroll
@@ -430,12 +507,12 @@ __global__ __launch_bounds__(W * kWave) void k_compress(const uint16_t* __restri
     }
     int need = k;  // keys still to keep beyond `above`
 #pragma unroll
-    for (int b = 14; b >= 0; --b) {
+    for (int b = NP - 2; b >= 0; --b) {
       uint32_t ones[NW];
       int c1 = 0;
 #pragma unroll
       for (int g = 0; g < NW; ++g) {
-        ones[g] = cand[g] & pl[16 * g + b];
+        ones[g] = cand[g] & pl[NP * g + b];
         c1 += __popc(ones[g]);
       }
       if constexpr (LPT == 2) c1 += __builtin_amdgcn_update_dpp(0, c1, 0xB1, 0xF, 0xF, true);
@@ -587,7 +664,7 @@ __global__ __launch_bounds__(W * kWave) void k_compress(const uint16_t* __restri
     const int64_t tile0 = ((int64_t)bh * cap_tokens + tok0 + j0) * T + (int)lane * TPL;
 #pragma unroll
     for (int t = 0; t < TPL; ++t) {
-      if constexpr (!PRESET) bitmaps[tile0 + t] = (uint64_t)keep[2 * t] | ((uint64_t)keep[2 * t + 1] << 32);
+      if constexpr (MODE != kPreset) bitmaps[tile0 + t] = (uint64_t)keep[2 * t] | ((uint64_t)keep[2 * t + 1] << 32);
       offsets[tile0 + t] = base + wave_off + lane_off + tile_pos[t];
     }
   }
@@ -643,33 +720,6 @@ __device__ __forceinline__ void select_variant(const PruneOpts& o, int k, const 
 
 __device__ __forceinline__ int stream_keep(const PruneOpts& o, int bh, int n_keep) {
   return o.per_head ? o.head_keep[bh % o.H] : n_keep;
-}
-
-// Bitmaps of tokens tok0 .. tok0+n_new-1 of every stream under a pruner
-// variant: one wave per token, lane = channel, kTokPerWave tokens per wave.
-constexpr int kTokPerWave = 8;
-
-template <int T>
-__global__ __launch_bounds__(256) void k_select(CacheView c, const uint16_t* __restrict__ x, int n_new,
-                                                int64_t x_stride, int tok0, PruneOpts o) {
-  constexpr int d = kTile * T;
-  const int64_t wave = (int64_t)blockIdx.x * (256 / kWave) + threadIdx.x / kWave;
-  const uint32_t lane = lane_id();
-  const int64_t total = (int64_t)c.BH * n_new;
-  for (int64_t i = wave * kTokPerWave; i < min(total, (wave + 1) * kTokPerWave); ++i) {
-    const int bh = (int)(i / n_new), j = (int)(i % n_new);
-    const int64_t row = (int64_t)bh * x_stride + j;
-    uint16_t xv[T];
-#pragma unroll
-    for (int t = 0; t < T; ++t) xv[t] = x[row * d + kTile * t + lane];
-    uint64_t bm[T];
-    select_variant<T>(o, stream_keep(o, bh, c.n_keep), xv, o.weights ? o.weights + row * d : nullptr,
-                      lane, bm);
-    uint64_t mine = bm[0];
-#pragma unroll
-    for (int t = 1; t < T; ++t) mine = (lane == (uint32_t)t) ? bm[t] : mine;
-    if (lane < (uint32_t)T) c.bitmaps[((int64_t)bh * c.cap_tokens + tok0 + j) * T + lane] = mine;
-  }
 }
 
 // ---- Per-channel value pruning in groups of 32 tokens (Sec. 2) ---------------------------
@@ -1236,13 +1286,14 @@ __global__ __launch_bounds__(256) void k_window_fill(WindowView w, int b, int d,
   }
 }
 
-// Clears the workspace and runs k_compress (PRESET: with the bitmaps already in the
-// cache).
-template <int T, bool PRESET>
+// Clears the workspace and runs k_compress.
+template <int T, int MODE>
 static hipError_t compress_launch(const CacheView& c, const uint16_t* x, int n_new, int64_t x_stride,
                                   int tok0, uint32_t* ws, hipStream_t s, const PruneOpts& o,
                                   uint32_t max_polls) {
-  const int W = compress_waves(T, c.BH, max_polls != kLookbackPolls);
+  // (eight waves at most for the variants: the scored selection's registers)
+  const int wide = compress_waves(T, c.BH, max_polls != kLookbackPolls);
+  const int W = MODE >= kScored && wide > 8 ? 8 : wide;
   const int chunk = compress_chunk_tokens(T) / 2 * W;
   const int n_chunks = (n_new + chunk - 1) / chunk;
   const int64_t n_wg = (int64_t)c.BH * n_chunks;
@@ -1252,17 +1303,16 @@ static hipError_t compress_launch(const CacheView& c, const uint16_t* x, int n_n
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   auto launch = [&](auto kernel, int waves) {
-    hipLaunchKernelGGL(kernel, dim3((uint32_t)n_wg), dim3(waves * kWave), 0, s, x, n_new, PRESET ? 0 : c.n_keep,
+    hipLaunchKernelGGL(kernel, dim3((uint32_t)n_wg), dim3(waves * kWave), 0, s, x, n_new, MODE == kPreset ? 0 : c.n_keep,
                        c.bitmaps, c.offsets, c.values, c.stream_len, c.cap_tokens, tok0, c.val_stride,
                        w.flags, w.ticket, n_chunks, x_stride, o, max_polls, w.decided, w.status);
   };
-  if constexpr (T == 4) {
-    if (W == 4) launch(k_compress<T, PRESET, 4>, 4);
-    else launch(k_compress<T, PRESET, 2>, 2);
-  } else {
-    if (W == 16) launch(k_compress<T, PRESET, 16>, 16);
-    else if (W == 8) launch(k_compress<T, PRESET, 8>, 8);
-    else launch(k_compress<T, PRESET, 2>, 2);
+  constexpr int kWide = T == 4 ? 4 : 8;
+  if (W == kWide) launch(k_compress<T, MODE, kWide>, kWide);
+  if constexpr (MODE < kScored) {
+    if (W == 2) launch(k_compress<T, MODE, 2>, 2);
+    if constexpr (T <= 2)
+      if (W == 16) launch(k_compress<T, MODE, 16>, 16);
   }
   return hipGetLastError();
 }
@@ -1271,7 +1321,7 @@ template <int T>
 static hipError_t compress_T(const CacheView& c, const uint16_t* x, int n_new, int64_t x_stride,
                              int tok0, uint32_t* ws, hipStream_t s, const PruneOpts& o = PruneOpts{},
                              uint32_t max_polls = kLookbackPolls) {
-  return compress_launch<T, false>(c, x, n_new, x_stride, tok0, ws, s, o, max_polls);
+  return compress_launch<T, kMagnitude>(c, x, n_new, x_stride, tok0, ws, s, o, max_polls);
 }
 
 // Options of a launch that compresses another number of tokens for each entry.
@@ -1344,7 +1394,7 @@ hipError_t launch_append_kv(const CacheView& kc, const CacheView& vc, const uint
 template <int T>
 static hipError_t pack_preset_T(const CacheView& c, const uint16_t* x, int n_new, int64_t x_stride,
                                 int tok0, uint32_t* ws, hipStream_t s, uint32_t max_polls = kLookbackPolls) {
-  return compress_launch<T, true>(c, x, n_new, x_stride, tok0, ws, s, entry_opts(c), max_polls);
+  return compress_launch<T, kPreset>(c, x, n_new, x_stride, tok0, ws, s, entry_opts(c), max_polls);
 }
 
 template <int T>
@@ -1382,12 +1432,9 @@ static hipError_t compress_variant_T(const CacheView& c, const uint16_t* x, int 
   // Magnitude pruning with a kept count per head is the bulk compressor with
   // its stream's count.
   if (o.mode == kPruneMagnitude) return compress_T<T>(c, x, n_new, (int64_t)n_new, tok0, ws, s, o);
-  const int64_t waves = ((int64_t)c.BH * n_new + kTokPerWave - 1) / kTokPerWave;
-  hipLaunchKernelGGL(k_select<T>, dim3((uint32_t)((waves + 3) / 4)), dim3(256), 0, s, c, x, n_new,
-                     (int64_t)n_new, tok0, o);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return pack_preset_T<T>(c, x, n_new, (int64_t)n_new, tok0, ws, s);
+  if (o.mode == kPruneOutputAware)
+    return compress_launch<T, kScored>(c, x, n_new, (int64_t)n_new, tok0, ws, s, o, kLookbackPolls);
+  return compress_launch<T, kTwoFour>(c, x, n_new, (int64_t)n_new, tok0, ws, s, o, kLookbackPolls);
 }
 
 hipError_t launch_compress_variant(const CacheView& c, const uint16_t* x, int n_new, int tok0,

@@ -100,8 +100,8 @@ struct PruneOpts {
   const float* weights = nullptr;  // output-aware: fp32 [BH][x_stride][64T] channel weights
   int32_t head_keep[kMaxPruneHeads] = {};
 };
-// Selection (bitmaps of tokens tok0.., one wave per token) then packing with the
-// given bitmaps (k_compress in its preset mode).
+// The bulk compression with a variant's selection (k_compress in its scored and
+// 2:4 modes).
 hipError_t launch_compress_variant(const CacheView& c, const uint16_t* x, int n_new, int tok0,
                                    uint32_t* ws, hipStream_t s, const PruneOpts& o);
 hipError_t launch_append_variant(const CacheView& c, const uint16_t* x, int tok0, hipStream_t s,

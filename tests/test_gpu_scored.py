@@ -1,0 +1,67 @@
+"""Output-aware and 2:4 selection in the bulk compression, where it can go wrong:
+ties of every key in a token and over a group's edge, zero weights, scores that
+differ only in their low 16 bits, subnormal and largest magnitudes, a token count
+that leaves waves of a chunk empty, kept counts per head, appended calls. Bit for bit
+against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2505_22913_amd as mf
+from tests.gpu_common import all_pairs, announce, compare_format, read_cache, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _inputs(rng, B, H, n, d):
+    x = rng.standard_normal((B, H, n, d), dtype=np.float32).astype(np.float16)
+    w = rng.random((B, H, n, d), dtype=np.float32) * 40
+    x[..., 0::7, :] = np.float16(1)                       # scores decided by the weights alone
+    w[..., 0::7, :] = np.float32(3)
+    w[..., 0::7, ::5] += np.float32(2 ** -21) * rng.integers(0, 8, w[..., 0::7, ::5].shape)
+    w[..., 1::11, :] = 0                                  # all scores equal (zero)
+    x[..., 2::9, :] = rng.choice(np.array([0.0, -0.0, 6e-8, -6e-8, 65504, -65504], np.float16), x[..., 2::9, :].shape)
+    return x, w
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("B,H,s", [(1, 2, 0.7), (2, 9, 0.5), (1, 1, 0.97)])
+def test_scored_selection_bit_exact(d, B, H, s):
+    import torch
+    for n in (1, 33, 257, 700):
+        announce(f"scored d={d} B={B} H={H} s={s} n={n}")
+        rng = np.random.default_rng(n + d)
+        x, w = _inputs(rng, B, H, n, d)
+        want = oracle.compress_variant(x, "output_aware", k=oracle.keep_count(d, s), weights=w)
+        Kc = mf.CompressedCache(B, H, d, s, n)
+        m = n // 2 if n > 40 else n
+        for lo, hi in ((0, m), (m, n)):
+            if hi > lo:
+                mf.mustafar_prune_compress_ex(Kc, to_dev(np.ascontiguousarray(x[:, :, lo:hi])), mode=mf.PRUNE_OUTPUT_AWARE,
+                                              weights=torch.from_numpy(np.ascontiguousarray(w[:, :, lo:hi])).cuda())
+        compare_format(read_cache(Kc), want, n, all_pairs(B, H))
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+def test_scored_counts_per_head(d):
+    import torch
+    B, H, n = 2, 4, 130
+    announce(f"scored per head d={d}")
+    rng = np.random.default_rng(d)
+    x, w = _inputs(rng, B, H, n, d)
+    hk = [d // 2, d // 4, 1, 0]
+    Kc = mf.CompressedCache(B, H, d, 0.5, n)
+    mf.mustafar_prune_compress_ex(Kc, to_dev(x), mode=mf.PRUNE_OUTPUT_AWARE, head_keep=hk,
+                                  weights=torch.from_numpy(w).cuda())
+    compare_format(read_cache(Kc), oracle.compress_variant(x, "output_aware", head_keep=hk, weights=w), n, all_pairs(B, H))
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("B,H", [(1, 2), (2, 9)])
+def test_two_four_ties_bit_exact(d, B, H):
+    for n in (1, 65, 300, 700):
+        announce(f"2:4 d={d} B={B} H={H} n={n}")
+        x, _ = _inputs(np.random.default_rng(n), B, H, n, d)
+        Kc = mf.CompressedCache(B, H, d, 0.5, n)
+        mf.mustafar_prune_compress_ex(Kc, to_dev(x), mode=mf.PRUNE_2_4)
+        compare_format(read_cache(Kc), oracle.compress_variant(x, "2:4"), n, all_pairs(B, H))
