@@ -277,10 +277,10 @@ enum mustafar_attn_kind {
  * 2048 of at least 128; the dense kernel with grouped queries about 4096 of at
  * least 128; a forced route (mustafar_attn_set_route) counts as 8 heads
  * (MATRIX_CORES) or as 2 (WALKS). A call that is passed n_splits <= 0 takes this
- * many segments on the walks and on the dense kernel; on the matrix-core kernel
- * it takes what fills the GPU once, which is at most the larger of the two
- * kinds' counts and never more than its workspace holds. Returns 1 for invalid
- * arguments or kind. */
+ * many segments on the walks and at most as many on the dense kernel; on the
+ * matrix-core kernel it takes what fills the GPU once, which is at most the larger
+ * of the two kinds' counts and never more than its workspace holds. Returns 1 for
+ * invalid arguments or kind. */
 int mustafar_attn_default_splits(int B, int Hq, int Hkv, int n_tokens, int kind);
 
 /* Kernel route of the sparse calls. DEFAULT: the matrix-core kernel (tiles

@@ -6,7 +6,8 @@
 // softmax), and k_merge combines the segments with their log-sum-exp weights.
 // The sparse call launches the compressed segments and the dense-window
 // segment in one grid, so the softmax spans concat(S_C, S_L) as Algorithm 1
-// states (the merge is order-free). The dense baseline reuses the dense body.
+// states (the merge is order-free). The dense baseline has a kernel of its own on the
+// matrix cores.
 //
 // Compressed blocks of NB = 64/T tokens ("load as compressed, expand in LDS"):
 //   * the packed values of a block are one contiguous run of the stream; the
@@ -745,15 +746,171 @@ __global__ __launch_bounds__(64) void k_sparse_attn(AttnArgs a) {
   write_partial<T, G>(a, seg, bh, m_run, l_run, o);
 }
 
-// Dense baseline: grid (n_dense_segs, BHkv).
+// ------------------------------------------------------------------------------------------
+// Dense baseline on the matrix cores. One wave per segment, blocks of 32 tokens: a
+// key row's 16-byte pieces are the A operand of the scores as they are loaded (lane =
+// token r, channels 32 c + 8 q), the scores in their result layout (lane = head r,
+// tokens 4 q + e) the A operand of the second product, and lane (q, r) loads channels
+// 4 T r .. of eight tokens and transposes them with byte permutes into its B operand.
+// The probabilities stay what they were in fp32: each enters as two fp16 parts
+// (value and remainder, 22 bits), the sum takes the fp32 one. About 200 vector
+// instructions for 16 KB, so the loads bound it; the kernel before it read V two
+// bytes a lane and did every product on the vector units. Cold, us, before and now:
+// 32 streams of 16K tokens, 4 heads per kv-head, d = 128 68 -> 45 (6.0 TB/s), 8
+// heads 79 -> 46; 128 of 16K, one head 190 -> 154 (7.0 TB/s); d = 64, 2 heads 33 ->
+// 26. Error against 64 bits the same (2.1e-4, the fp16 output's rounding).
+// Grid (n_dense_segs, BHkv).
+// ------------------------------------------------------------------------------------------
+typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr float kDensePBias = 15.f;   // the largest probability part is 2^15, inside fp16
+
+__device__ __forceinline__ half8_t dense_h8(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+  const u32x4 w = {a, b, c, d};
+  return __builtin_bit_cast(half8_t, w);
+}
+
+// Wait states before the first vector use of MFMA results where a branch may come
+// between (the compiler inserts them within a block only).
+template <int N>
+__device__ __forceinline__ void dense_settle(f32x4 (&r)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(r[i]));
+  asm volatile("s_nop 15" : "+v"(r[0]));
+}
+
 template <int T, int G>
 __global__ __launch_bounds__(64) void k_dense_attn(AttnArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int d = kTile * T, NC = 2 * T, NO = 4 * T, NB = 32;
   const int seg = blockIdx.x, bh = blockIdx.y;
-  float m_run[G], l_run[G], o[G][T];
-  init_state<T, G>(m_run, l_run, o);
-  dense_body<T, G, false>(a, seg, bh, smem, m_run, l_run, o);
-  write_partial<T, G>(a, seg, bh, m_run, l_run, o);
+  const uint32_t lane = lane_id(), r16 = lane % 16, q4 = lane / 16;
+  const int j0 = seg * a.dense_seg_tokens, j1 = min(j0 + a.dense_seg_tokens, a.n_dense);
+  const uint16_t* kd = a.kd + (int64_t)bh * a.n_dense * d;
+  const uint16_t* vd = a.vd + (int64_t)bh * a.n_dense * d;
+
+  u32x4 kr[2][NC];
+  uint32_t vr[8][2 * T];
+  // Rows past the segment's end repeat its last token (their p is 0).
+  auto load_keys = [&](int b0) {
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      const uint16_t* row = kd + (int64_t)min(b0 + 16 * g + (int)r16, j1 - 1) * d + 8 * q4;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) kr[g][c] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(row + 32 * c));
+    }
+  };
+  auto load_values = [&](int b0) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const uint16_t* row = vd + (int64_t)min(b0 + 4 * (int)q4 + (i < 4 ? i : 12 + i), j1 - 1) * d + NO * r16;
+      if constexpr (T == 1) {
+        const u32x2 v = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(row));
+        vr[i][0] = v.x;
+        vr[i][1] = v.y;
+      } else {
+#pragma unroll
+        for (int n = 0; n < T / 2; ++n) {
+          const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(row) + n);
+          vr[i][4 * n] = v.x;
+          vr[i][4 * n + 1] = v.y;
+          vr[i][4 * n + 2] = v.z;
+          vr[i][4 * n + 3] = v.w;
+        }
+      }
+    }
+  };
+  load_keys(j0);
+  load_values(j0);
+  half8_t qb[NC];
+  {
+    const uint16_t* qsrc = a.q + ((int64_t)bh * G + (r16 < (uint32_t)G ? r16 : 0u)) * d + 8 * q4;
+    const uint32_t keep = r16 < (uint32_t)G ? 0xffffffffu : 0u;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const u32x4 w = *reinterpret_cast<const u32x4*>(qsrc + 32 * c);
+      qb[c] = dense_h8(w.x & keep, w.y & keep, w.z & keep, w.w & keep);
+    }
+  }
+  float m_run = -INFINITY, l_run = 0.f;
+  f32x4 o[NO];
+#pragma unroll
+  for (int c = 0; c < NO; ++c) o[c] = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+  for (int b0 = j0; b0 < j1; b0 += NB) {
+    f32x4 sc[2];
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      sc[g] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        sc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(dense_h8(kr[g][c].x, kr[g][c].y, kr[g][c].z, kr[g][c].w), qb[c],
+                                                       sc[g], 0, 0, 0);
+    }
+    dense_settle(sc);
+    if (b0 + NB < j1) load_keys(b0 + NB);
+    if (b0 + NB > j1) {
+#pragma unroll
+      for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (b0 + 16 * g + 4 * (int)q4 + e >= j1) sc[g][e] = -INFINITY;
+    }
+    float bmax = -INFINITY;
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) bmax = fmaxf(bmax, sc[g][e]);
+    bmax *= a.scale_log2;  // the scale is positive
+    if (ballot(bmax > m_run)) {
+      bmax = fmaxf(bmax, __shfl_xor(bmax, 16, kWave));
+      bmax = fmaxf(bmax, __shfl_xor(bmax, 32, kWave));
+      const float mnew = fmaxf(m_run, bmax);
+      const float alpha = __builtin_amdgcn_exp2f(m_run - mnew);
+      m_run = mnew;
+      l_run *= alpha;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float ar = __shfl(alpha, (int)(4u * q4) + e, kWave);  // row 4 q4 + e is that head
+#pragma unroll
+        for (int c = 0; c < NO; ++c) o[c][e] *= ar;
+      }
+    }
+    half8_t ph, pl;
+    const float sub = kDensePBias - m_run;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float p = __builtin_amdgcn_exp2f(fmaf(sc[i / 4][i % 4], a.scale_log2, sub));
+      l_run += p;
+      ph[i] = (_Float16)p;
+      pl[i] = (_Float16)(p - (float)ph[i]);
+    }
+#pragma unroll
+    for (int n = 0; n < NO; ++n) {
+      uint32_t y[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        y[i] = __builtin_amdgcn_perm(vr[2 * i + 1][n / 2], vr[2 * i][n / 2], (n & 1) ? 0x07060302u : 0x05040100u);
+      const half8_t vb = dense_h8(y[0], y[1], y[2], y[3]);
+      o[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ph, vb, o[n], 0, 0, 0);
+      o[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pl, vb, o[n], 0, 0, 0);
+    }
+    if (b0 + NB < j1) load_values(b0 + NB);
+  }
+  dense_settle(o);
+  l_run += __shfl_xor(l_run, 16, kWave);
+  l_run += __shfl_xor(l_run, 32, kWave);
+  const int64_t row0 = (int64_t)seg * a.BHq + (int64_t)bh * G;
+  if (q4 == 0 && r16 < (uint32_t)G) a.ws_ml[row0 + r16] = make_float2(m_run - kDensePBias, l_run);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const uint32_t h = 4u * q4 + (uint32_t)e;
+    if (h < (uint32_t)G) {
+      f32x4* dst = reinterpret_cast<f32x4*>(a.ws_o + (row0 + h) * d + NO * r16);
+#pragma unroll
+      for (int n = 0; n < T; ++n) dst[n] = (f32x4){o[4 * n][e], o[4 * n + 1][e], o[4 * n + 2][e], o[4 * n + 3][e]};
+    }
+  }
 }
 
 // grid (BHq, parts), 8 waves: log-sum-exp merge of segments [part * per,
@@ -888,8 +1045,7 @@ static hipError_t attention_TG(const AttnShape& sh, const AttnArgs& a, uint16_t*
     // Sparse call with an empty compressed cache: only the window segment.
     e = sparse_launch<T, G, 4>(sh, a, s);
   } else {
-    hipLaunchKernelGGL((k_dense_attn<T, G>), dim3(sh.n_dense_segs, sh.BHkv), dim3(kWave),
-                       dense_lds_bytes(T, G), s, a);
+    hipLaunchKernelGGL((k_dense_attn<T, G>), dim3(sh.n_dense_segs, sh.BHkv), dim3(kWave), 0, s, a);
     e = hipGetLastError();
   }
   if (e != hipSuccess) return e;

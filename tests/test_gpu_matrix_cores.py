@@ -62,3 +62,20 @@ def test_full_tiles_beside_empty_ones(d):
     ref = oracle.sparse_decode_attention(q, oracle.compress(K, s), oracle.compress(V, s),
                                          np.zeros((1, 1, 0, d), np.float16), np.zeros((1, 1, 0, d), np.float16))
     assert attn_error(out.cpu().numpy(), ref) <= ATTN_TOL
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_dense_blocks(d, G):
+    # The dense kernel's blocks are 32 tokens in two groups of 16; rows past a
+    # segment's end repeat its last token. Probabilities in two fp16 parts.
+    import torch
+    B, H = 2, 2
+    for n, splits in ((1, 0), (15, 1), (17, 0), (32, 1), (33, 0), (64, 0), (65, 2), (127, 1), (300, 3), (1000, 0)):
+        announce(f"dense blocks d={d} G={G} n={n} splits={splits}")
+        K, V = synth.make_kv(B, H, n, d, seed=n + d)
+        q = synth.make_q(B, H * G, d, seed=n)
+        out = mf.mustafar_dense_decode_attn(to_dev(q), to_dev(K), to_dev(V), n_splits=splits)
+        torch.cuda.synchronize()
+        err = attn_error(out.cpu().numpy(), oracle.decode_attention(q, K, V))
+        assert err <= ATTN_TOL, (n, err)
