@@ -1049,7 +1049,7 @@ static hipError_t attention_TG(const AttnShape& sh, const AttnArgs& a, uint16_t*
     e = hipGetLastError();
   }
   if (e != hipSuccess) return e;
-  const int parts = merge_parts(n_seg, a.BHq);
+  const int parts = merge_parts(n_seg, a.BHq, kMergeMostSingle);
   if (parts > 1) {
     // Two levels: parts of kMergeSegsPerPart segments, then the parts.
     float2* part_ml = reinterpret_cast<float2*>(a.ws_o + (int64_t)n_seg * a.BHq * (kTile * T));

@@ -193,10 +193,13 @@ struct AttnShape {
 };
 
 // Split-K merge in two levels when a single level would run on too few
-// workgroups (many segments, few query heads): the number of first-level parts
-// of 32 segments, or 1 for a single-level merge.
-inline int merge_parts(int64_t n_seg, int64_t BHq) {
-  return (n_seg > 128 && BHq < 256) ? (int)((n_seg + 31) / 32) : 1;
+// workgroups for its segments: the number of first-level parts of 32 segments, or
+// 1 for a single-level merge. The workspace provides for two levels from 128
+// segments on; the launch takes one up to 512 (8 streams of 128K tokens, 342 segments
+// of 32 query heads: 56.4 us a call with one, 58.4 with two and the launch between).
+constexpr int kMergeMostSingle = 512;
+inline int merge_parts(int64_t n_seg, int64_t BHq, int most_single = 128) {
+  return (n_seg > most_single && BHq < 256) ? (int)((n_seg + 31) / 32) : 1;
 }
 
 // Partial results of every segment into ws_ml [n_seg][BHq] (max, sum) and
