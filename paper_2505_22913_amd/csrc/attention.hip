@@ -9,7 +9,8 @@
 // states (the merge is order-free). The dense baseline has a kernel of its own on the
 // matrix cores.
 //
-// Compressed blocks of NB = 64/T tokens ("load as compressed, expand in LDS"):
+// The walks, for MUSTAFAR_ROUTE_WALKS (the matrix-core kernel is the faster one at every
+// group size: attention_mfma.hip). Compressed blocks of NB = 64/T tokens:
 //   * the packed values of a block are one contiguous run of the stream; the
 //     next block's runs are fetched into registers with 16-byte coalesced
 //     loads while the current block is computed, then written to LDS;
@@ -753,7 +754,7 @@ __global__ __launch_bounds__(64) void k_sparse_attn(AttnArgs a) {
 // tokens 4 q + e) the A operand of the second product, and lane (q, r) loads channels
 // 4 T r .. of eight tokens and transposes them with byte permutes into its B operand.
 // The probabilities stay what they were in fp32: each enters as two fp16 parts
-// (value and remainder, 22 bits), the sum takes the fp32 one. About 200 vector
+// (value and remainder, 21 bits), the sum takes the fp32 one. About 200 vector
 // instructions for 16 KB, so the loads bound it; the kernel before it read V two
 // bytes a lane and did every product on the vector units. Cold, us, before and now:
 // 32 streams of 16K tokens, 4 heads per kv-head, d = 128 68 -> 45 (6.0 TB/s), 8
@@ -765,6 +766,11 @@ typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr float kDensePBias = 15.f;   // the largest probability part is 2^15, inside fp16
+// The least part of a probability, fp16's least subnormal, 2^-39 of the largest. The
+// first part is rounded towards zero, so both parts are positive and an infinite
+// value (a cache that overflowed) stays infinite: a zero or negative part would turn it
+// into NaN.
+constexpr float kDenseLeast = 0x1p-24f;
 
 __device__ __forceinline__ half8_t dense_h8(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
   const u32x4 w = {a, b, c, d};
@@ -879,11 +885,20 @@ __global__ __launch_bounds__(64) void k_dense_attn(AttnArgs a) {
     half8_t ph, pl;
     const float sub = kDensePBias - m_run;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float p = __builtin_amdgcn_exp2f(fmaf(sc[i / 4][i % 4], a.scale_log2, sub));
-      l_run += p;
-      ph[i] = (_Float16)p;
-      pl[i] = (_Float16)(p - (float)ph[i]);
+    for (int i = 0; i < 8; i += 2) {
+      float p[2];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        p[e] = __builtin_amdgcn_exp2f(fmaf(sc[i / 4][i % 4 + e], a.scale_log2, sub));
+        l_run += p[e];
+        p[e] = fmaxf(p[e], kDenseLeast);
+      }
+      const half2_t h = __builtin_bit_cast(half2_t, __builtin_amdgcn_cvt_pkrtz(p[0], p[1]));
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        ph[i + e] = h[e];
+        pl[i + e] = (_Float16)fmaxf(p[e] - (float)h[e], kDenseLeast);
+      }
     }
 #pragma unroll
     for (int n = 0; n < NO; ++n) {

@@ -79,3 +79,26 @@ def test_dense_blocks(d, G):
         torch.cuda.synchronize()
         err = attn_error(out.cpu().numpy(), oracle.decode_attention(q, K, V))
         assert err <= ATTN_TOL, (n, err)
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("at", [64, 66, 69])
+def test_dense_infinite_values(d, at):
+    # A value that overflowed to infinity gives an infinite output in its channel (at
+    # the token with the largest probability, beside it, and at the last row, which
+    # the lanes past the end repeat) and leaves the other channels as they are. In the
+    # second segment: the merge weighs the first one's output with zero where it pads.
+    import torch
+    n, G = 70, 4
+    K, V = synth.make_kv(1, 1, n, d, seed=at + d)
+    q = synth.make_q(1, G, d, seed=5)
+    K[0, 0, 64] = q[0, 0]                    # head 0's largest probability
+    ref = oracle.decode_attention(q, K, V)
+    V[0, 0, at, 3], V[0, 0, at, d - 1] = np.inf, -np.inf
+    announce(f"dense infinite value d={d} at={at}")
+    out = mf.mustafar_dense_decode_attn(to_dev(q), to_dev(K), to_dev(V), n_splits=2)
+    torch.cuda.synchronize()
+    out = out.cpu().numpy()
+    assert (out[..., 3] == np.inf).all() and (out[..., d - 1] == -np.inf).all()
+    rest = np.r_[0:3, 4:d - 1]
+    assert np.abs(out[..., rest] - np.asarray(ref)[..., rest]).max() <= ATTN_TOL * np.abs(ref).max()
