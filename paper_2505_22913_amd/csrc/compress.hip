@@ -25,6 +25,8 @@
 namespace mf {
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+// The same where the caller guarantees 4-byte alignment only (still one load).
+typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
 template <typename V>
 __device__ __forceinline__ V lds_ld(uint32_t byte_addr) {
@@ -292,7 +294,7 @@ __device__ __forceinline__ void lds_barrier() {
 // one stream, one run per wave. The waves select and pack their runs side by side
 // and share the chunk's ticket, scan total and look-back, so those cost once per
 // chunk (two waves: 4% off the bulk compression of a 50% cache against one; which
-// W when: compress_launch).
+// W when: compress_waves in mf_launch.h).
 // MODE kPreset: the keep-masks are the bitmaps already in the cache for these tokens
 // (a pruner variant selected them); only the scan and the packing run. MODE
 // kScored: output-aware selection, the same bit-sliced search over the 31 bits of
@@ -448,7 +450,7 @@ __global__ __launch_bounds__(W * kWave) void k_compress(const uint16_t* __restri
         for (int i = 0; i < 8; ++i) {
           const int seg = i * 8 + (int)lane / 8;
           const int tok = min(seg / LPT, max(nt, 1) - 1);
-          r[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(wsrc + (int64_t)tok * d + (seg % LPT) * CPL + 32 * g) + lane % 8);
+          r[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_a4*>(wsrc + (int64_t)tok * d + (seg % LPT) * CPL + 32 * g) + lane % 8);
         }
       };
       u32x4_t wr[8];

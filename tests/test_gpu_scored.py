@@ -43,6 +43,24 @@ def test_scored_selection_bit_exact(d, B, H, s):
 
 
 @pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("skip", [1, 2, 3])
+def test_scored_weights_at_any_float(d, skip):
+    # The weights need 4-byte alignment only.
+    import torch
+    B, H, n, s = 1, 2, 77, 0.7
+    announce(f"scored weights {4 * skip} bytes into a buffer, d={d}")
+    x, w = _inputs(np.random.default_rng(d + skip), B, H, n, d)
+    buf = torch.zeros(w.size + 4, dtype=torch.float32, device="cuda")
+    wd = buf[skip:skip + w.size].view(w.shape)
+    wd.copy_(torch.from_numpy(w))
+    assert wd.data_ptr() % 16 == 4 * skip
+    Kc = mf.CompressedCache(B, H, d, s, n)
+    mf.mustafar_prune_compress_ex(Kc, to_dev(x), mode=mf.PRUNE_OUTPUT_AWARE, weights=wd)
+    want = oracle.compress_variant(x, "output_aware", k=oracle.keep_count(d, s), weights=w)
+    compare_format(read_cache(Kc), want, n, all_pairs(B, H))
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
 def test_scored_counts_per_head(d):
     import torch
     B, H, n = 2, 4, 130
