@@ -439,7 +439,7 @@ def route_ab(args) -> None:
         r["call_us_median"] = float(np.median(r["call_us"]))
         r["gb_s"] = alg / (r["call_us_median"] * 1e-6) / 1e9
     print(json.dumps({"route_ab": res, "workload": w.name, "q_heads_per_kv_head": w.G, "alg_bytes": alg,
-                      "default": "matrix_cores" if w.G >= 8 else "walks"}), flush=True)
+                      "default": "matrix_cores"}), flush=True)
 
 
 def attn_only(args) -> None:
@@ -848,13 +848,13 @@ def main():
                       "kv_tokens_per_s": w.B * w.Hkv * (n_s_end + w.n_tail) / attn_s,
                       "alg_bytes": alg_bytes, "gb_s": attn_gbs,
                       "how": "HIP events around mustafar_window_decode_attn on its stream "
-                             "(k_sparse_attn + the split-K merge), every timed step"},
+                             "(k_sparse_attn_mfma + the split-K merge), every timed step"},
         "roofline": {"bound": "hbm", "achieved": attn_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": attn_gbs / HBM_PEAK_GBS,
-                     "kernel": "k_sparse_attn",
+                     "kernel": "k_sparse_attn_mfma",
                      "how": "algorithmic bytes of one launch / mean time of the timed attention "
-                            "calls (k_sparse_attn and its split-K merge, about 0.6% of it)",
-                     "traffic": measured_traffic("k_sparse_attn", w.name),
+                            "calls (k_sparse_attn_mfma and its split-K merge, about 0.6% of it)",
+                     "traffic": measured_traffic("k_sparse_attn_mfma", w.name),
                      "needed_bytes": read_bytes,
                      "frac_of_needed_bytes": read_bytes / attn_s / 1e9 / HBM_PEAK_GBS,
                      "needed_how": "algorithmic bytes less the per-tile offsets, which the "

@@ -43,7 +43,7 @@ constexpr int kKeyWeightSteps = 32;        // output-aware keys: the current and
 static_assert(MUSTAFAR_LOOKBACK_POLLS == mf::kLookbackPolls, "look-back bound");
 static_assert(MUSTAFAR_STREAM_POISONED == mf::kStreamPoisoned, "poisoned stream marker");
 
-// Kernel route of grouped queries (mustafar_attn_set_route), process-wide.
+// Kernel route of the sparse calls (mustafar_attn_set_route), process-wide.
 std::atomic<int> g_route{MUSTAFAR_ROUTE_DEFAULT};
 
 // Whether a sparse call runs its compressed segments on the matrix-core kernel:

@@ -1,6 +1,6 @@
-// Device helpers shared by the decode-attention kernels (attention.hip: the
-// bit-walk kernel, one or grouped query heads; attention_mfma.hip: the MFMA
-// kernel for grouped queries):
+// Device helpers shared by the decode-attention kernels (attention_mfma.hip: the
+// MFMA kernel, the default at every group size; attention.hip: the bit-walk
+// kernel, the dense kernel and the merge):
 // types, wave reductions, LDS access, the staging of compressed blocks, the
 // bit-walk primitives, the dense (window) segment body and the partial-result
 // writes of the split-K scheme.
