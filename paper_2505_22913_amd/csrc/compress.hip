@@ -634,7 +634,10 @@ __global__ __launch_bounds__(W * kWave) void k_compress(const uint16_t* __restri
         __hip_atomic_store(status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       } else if (chunk == own_chunks - 1) {
         __hip_atomic_store(stream_len + bh, b + run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __threadfence();  // before this chunk counts as decided
+        // Performed before this chunk counts as decided. Only this store matters, so
+        // waiting for it is enough: a release fence would write back the XCD's L2 for
+        // every stream (512 streams of 1K tokens at d = 128: 65.6 us, 48.3 without).
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       }
       n_decided = __hip_atomic_fetch_add(decided + bh, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -1329,9 +1332,9 @@ template <int T, int MODE>
 static hipError_t compress_launch(const CacheView& c, const uint16_t* x, int n_new, int64_t x_stride,
                                   int tok0, uint32_t* ws, hipStream_t s, const PruneOpts& o,
                                   uint32_t max_polls) {
-  // (eight waves at most for the variants: the scored selection's registers)
-  const int wide = compress_waves(T, c.BH, max_polls != kLookbackPolls);
-  const int W = MODE >= kScored && wide > 8 ? 8 : wide;
+  constexpr int kWide = T == 4 ? 4 : 8;
+  // (the variants have one width: the scored selection's registers)
+  const int W = MODE >= kScored ? kWide : compress_waves(T, c.BH, max_polls != kLookbackPolls);
   const int chunk = compress_chunk_tokens(T) / 2 * W;
   const int n_chunks = (n_new + chunk - 1) / chunk;
   const int64_t n_wg = (int64_t)c.BH * n_chunks;
@@ -1345,7 +1348,6 @@ static hipError_t compress_launch(const CacheView& c, const uint16_t* x, int n_n
                        c.bitmaps, c.offsets, c.values, c.stream_len, c.cap_tokens, tok0, c.val_stride,
                        w.flags, w.ticket, n_chunks, x_stride, o, max_polls, w.decided, w.status);
   };
-  constexpr int kWide = T == 4 ? 4 : 8;
   if (W == kWide) launch(k_compress<T, MODE, kWide>, kWide);
   if constexpr (MODE < kScored) {
     if (W == 2) launch(k_compress<T, MODE, 2>, 2);

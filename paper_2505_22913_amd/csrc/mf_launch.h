@@ -35,11 +35,13 @@ struct CacheView {
 // many chunks of each in flight that wait for one another: with two waves, 32
 // streams of 16K tokens at d = 128 (50%) took 110 us against 60 with eight, 8 of
 // 128K 295 against 163 (139 with 16, which leaves one workgroup a CU and costs
-// 10-20% from 32 streams on), 128 of 16K 217 against 172; 512 streams the same.
-// d = 256: four (60 against 76; eight 68). A caller's bound on the look-back
-// counts chunks of two waves.
+// 10-20% from 32 streams on), 128 of 16K 217 against 172, 256 of 16K 356 against 348.
+// 512 streams have few chunks of each in flight, and two waves leave more workgroups
+// a CU: 4K tokens each 186 against 198 with eight, d = 64 of 8K 171 against 188. d = 256: four (60 against 76; eight 68). A caller's bound on
+// the look-back counts chunks of two waves.
+constexpr int64_t kManyStreams = 512;
 constexpr int compress_waves(int T, int64_t BH, bool bounded) {
-  return bounded ? 2 : T == 4 ? 4 : BH <= 16 ? 16 : 8;
+  return bounded || BH >= kManyStreams ? 2 : T == 4 ? 4 : BH <= 16 ? 16 : 8;
 }
 
 // A stream whose bulk compression gave up waiting in the look-back (see

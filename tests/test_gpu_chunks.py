@@ -31,6 +31,18 @@ def test_chunk_edges_bit_exact(d, B, H):
 
 
 @pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("B,H", [(73, 7), (32, 16)])
+def test_chunk_edges_either_side_of_many_streams(d, B, H):
+    # 511 streams take the wide chunks, 512 the narrow ones.
+    for n in (63, 130):
+        announce(f"chunks d={d} B={B} H={H} n={n}")
+        K, _ = synth.make_kv(B, H, n, d, seed=n)
+        Kc = mf.CompressedCache(B, H, d, 0.6, n)
+        mf.mustafar_prune_compress(Kc, to_dev(K))
+        compare_format(read_cache(Kc), oracle.compress(K, 0.6), n, all_pairs(B, H))
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
 @pytest.mark.parametrize("B,H", [(1, 2), (3, 7)])
 def test_selected_bitmaps_at_chunk_edges(d, B, H):
     # 2:4 pruning: the packing runs on bitmaps that another kernel selected.
