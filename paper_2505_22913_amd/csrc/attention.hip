@@ -765,7 +765,8 @@ __global__ __launch_bounds__(64) void k_sparse_attn(AttnArgs a) {
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-constexpr float kDensePBias = 15.f;   // the largest probability part is 2^15, inside fp16
+constexpr float kDensePBias = 15.f;   // the largest probability part is 2^15, inside fp16 (taken
+constexpr float kDensePUnit = 0x1p-15f;  // against the unscaled maximum, as in attention_mfma.hip)
 // The least part of a probability, fp16's least subnormal, 2^-39 of the largest. The
 // first part is rounded towards zero, so both parts are positive and an infinite
 // value (a cache that overflowed) stays infinite: a zero or negative part would turn it
@@ -867,12 +868,11 @@ __global__ __launch_bounds__(64) void k_dense_attn(AttnArgs a) {
     for (int g = 0; g < 2; ++g)
 #pragma unroll
       for (int e = 0; e < 4; ++e) bmax = fmaxf(bmax, sc[g][e]);
-    bmax *= a.scale_log2;  // the scale is positive
     if (ballot(bmax > m_run)) {
       bmax = fmaxf(bmax, __shfl_xor(bmax, 16, kWave));
       bmax = fmaxf(bmax, __shfl_xor(bmax, 32, kWave));
       const float mnew = fmaxf(m_run, bmax);
-      const float alpha = __builtin_amdgcn_exp2f(m_run - mnew);
+      const float alpha = __builtin_amdgcn_exp2f((m_run - mnew) * a.scale_log2);  // the scale is positive
       m_run = mnew;
       l_run *= alpha;
 #pragma unroll
@@ -883,13 +883,12 @@ __global__ __launch_bounds__(64) void k_dense_attn(AttnArgs a) {
       }
     }
     half8_t ph, pl;
-    const float sub = kDensePBias - m_run;
 #pragma unroll
     for (int i = 0; i < 8; i += 2) {
       float p[2];
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
-        p[e] = __builtin_amdgcn_exp2f(fmaf(sc[i / 4][i % 4 + e], a.scale_log2, sub));
+        p[e] = __builtin_amdgcn_exp2f(fmaf(sc[i / 4][i % 4 + e] - m_run, a.scale_log2, kDensePBias));
         l_run += p[e];
         p[e] = fmaxf(p[e], kDenseLeast);
       }
@@ -916,14 +915,15 @@ __global__ __launch_bounds__(64) void k_dense_attn(AttnArgs a) {
   l_run += __shfl_xor(l_run, 16, kWave);
   l_run += __shfl_xor(l_run, 32, kWave);
   const int64_t row0 = (int64_t)seg * a.BHq + (int64_t)bh * G;
-  if (q4 == 0 && r16 < (uint32_t)G) a.ws_ml[row0 + r16] = make_float2(m_run - kDensePBias, l_run);
+  if (q4 == 0 && r16 < (uint32_t)G) a.ws_ml[row0 + r16] = make_float2(m_run * a.scale_log2, l_run * kDensePUnit);
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const uint32_t h = 4u * q4 + (uint32_t)e;
     if (h < (uint32_t)G) {
       f32x4* dst = reinterpret_cast<f32x4*>(a.ws_o + (row0 + h) * d + NO * r16);
 #pragma unroll
-      for (int n = 0; n < T; ++n) dst[n] = (f32x4){o[4 * n][e], o[4 * n + 1][e], o[4 * n + 2][e], o[4 * n + 3][e]};
+      for (int n = 0; n < T; ++n)
+        dst[n] = (f32x4){o[4 * n][e], o[4 * n + 1][e], o[4 * n + 2][e], o[4 * n + 3][e]} * kDensePUnit;
     }
   }
 }

@@ -39,11 +39,15 @@ typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// The probabilities enter the p.V product as fp16, computed against the exact
-// running maximum with this exponent bias: the largest is 2^15 (inside fp16),
-// and the small ones keep 15 more binades before they flush to zero. The
-// partial's maximum is written as m - kMfmaPBias, consistent with l and o.
+// The probabilities enter the p.V product as fp16 with this exponent bias: the
+// largest is 2^15 (inside fp16), and the small ones keep 15 more binades before they
+// flush to zero. The running maximum is kept unscaled and subtracted before the
+// scaling: the difference is zero for the largest score, whatever its size. (Against
+// the rounded product max * scale the exponent of a large score's p came out up to
+// half an ulp of that product above the bias, and p infinite.) The partial's l and
+// o are scaled back, exactly.
 constexpr float kMfmaPBias = 15.f;
+constexpr float kMfmaPUnit = 0x1p-15f;
 
 // Byte selectors of nibble n: channel c (kept) takes packed value popc(n below c)
 // of the four at hand (bytes 2 pos, 2 pos + 1), a dropped one zero (selector 12).
@@ -270,12 +274,11 @@ __device__ __forceinline__ void sparse_body_mfma(const AttnArgs& a, const MfmaLd
     for (int g = 0; g < NG; ++g)
 #pragma unroll
       for (int e = 0; e < 4; ++e) bmax = fmaxf(bmax, sc[g][e]);
-    bmax *= a.scale_log2;  // the scale is positive
     if (ballot(bmax > m_run)) {
       bmax = fmaxf(bmax, __shfl_xor(bmax, 16, kWave));
       bmax = fmaxf(bmax, __shfl_xor(bmax, 32, kWave));
       const float mnew = fmaxf(m_run, bmax);
-      const float alpha = __builtin_amdgcn_exp2f(m_run - mnew);
+      const float alpha = __builtin_amdgcn_exp2f((m_run - mnew) * a.scale_log2);  // the scale is positive
       m_run = mnew;
       l_run *= alpha;
       // Row 4 q4 + e of every O tile is head 4 q4 + e.
@@ -287,15 +290,14 @@ __device__ __forceinline__ void sparse_body_mfma(const AttnArgs& a, const MfmaLd
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[c][e] *= ar[e];
     }
-    // p = exp2(score - m + kMfmaPBias) in fp16 (at most 2^15); the sum is taken
+    // p = exp2((s - max) scale + kMfmaPBias) in fp16 (at most 2^15); the sum is taken
     // over the same rounded p that the p.V product multiplies (per lane, reduced
     // at the segment's end).
     half4_t pa[NG];
-    const float sub = kMfmaPBias - m_run;
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) pa[g][e] = (_Float16)__builtin_amdgcn_exp2f(fmaf(sc[g][e], a.scale_log2, sub));
+      for (int e = 0; e < 4; ++e) pa[g][e] = (_Float16)__builtin_amdgcn_exp2f(fmaf(sc[g][e] - m_run, a.scale_log2, kMfmaPBias));
       const half2_t one = {(_Float16)1.f, (_Float16)1.f};
       l_run = __builtin_amdgcn_fdot2((half2_t){pa[g][0], pa[g][1]}, one, l_run, false);
       l_run = __builtin_amdgcn_fdot2((half2_t){pa[g][2], pa[g][3]}, one, l_run, false);
@@ -422,7 +424,8 @@ __global__ __launch_bounds__(64, mfma_waves(T, KP)) void k_sparse_attn_mfma(Attn
 #pragma unroll
   for (int c = 0; c < Geo::NO; ++c) o[c] = (f32x4){0.f, 0.f, 0.f, 0.f};
   sparse_body_mfma<T, G, KP, VC>(a, L, seg, bh, m_run, l_run, o);
-  m_run -= kMfmaPBias;  // -inf stays -inf for an empty segment
+  m_run *= a.scale_log2;  // -inf stays -inf for an empty segment
+  l_run *= kMfmaPUnit;
 
   const uint32_t lane = lane_id();
   const uint32_t r16 = lane % 16, q4 = lane / 16;
@@ -434,7 +437,7 @@ __global__ __launch_bounds__(64, mfma_waves(T, KP)) void k_sparse_attn_mfma(Attn
     if (h < (uint32_t)G) {
       f32x4* dst = reinterpret_cast<f32x4*>(a.ws_o + (row0 + h) * d + Geo::NO * r16);
 #pragma unroll
-      for (int n = 0; n < T; ++n) dst[n] = (f32x4){o[4 * n][e], o[4 * n + 1][e], o[4 * n + 2][e], o[4 * n + 3][e]};
+      for (int n = 0; n < T; ++n) dst[n] = (f32x4){o[4 * n][e], o[4 * n + 1][e], o[4 * n + 2][e], o[4 * n + 3][e]} * kMfmaPUnit;
     }
   }
 }
