@@ -23,6 +23,8 @@
 //     has bits left;
 //   * p.V runs with one lane per channel over the expanded value tile, two
 //     tokens at a time with v_dot2 (fp16 probabilities, fp32 accumulation).
+#include <type_traits>
+
 #include "attn_common.h"
 
 namespace mf {
@@ -798,7 +800,9 @@ __global__ __launch_bounds__(64) void k_dense_attn(AttnArgs a) {
 
   u32x4 kr[2][NC];
   uint32_t vr[8][2 * T];
-  // Rows past the segment's end repeat its last token (their p is 0).
+  // Rows past the segment's end repeat its last token. Their scores are masked, so both
+  // their parts are the least: the at most 31 of them add 2^-33 of the largest
+  // probability's weight to the last token's values, and nothing to the sum.
   auto load_keys = [&](int b0) {
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
@@ -956,41 +960,52 @@ __global__ __launch_bounds__(kMergeWaves * kWave) void k_merge(const float2* __r
   const int s0 = blockIdx.y * per, s1 = min(n_seg, s0 + per);
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const uint32_t lane = lane_id();
-  float m = -INFINITY, l = 0.f, acc[T];
+  float m, l, acc[T];
+  // This wave's segments into (m, l, acc). SELECT: leave out the outputs loaded for
+  // segments past the range, which otherwise weigh 0 and turn an infinite one into NaN.
+  auto accumulate = [&](auto SELECT) {
+    m = -INFINITY;
+    l = 0.f;
 #pragma unroll
-  for (int tt = 0; tt < T; ++tt) acc[tt] = 0.f;
-  for (int c0 = s0 + wave; c0 < s1; c0 += kMergeChunk * kMergeWaves) {
-    // Lane k < kMergeChunk loads (max, sum) of the chunk's segment k; every lane
-    // loads its channel of each segment's output. Segments past the range load
-    // the first one again and weigh 0.
-    const int sk = c0 + (int)(lane % kMergeChunk) * kMergeWaves;
-    const bool lv = lane < (uint32_t)kMergeChunk && sk < s1;
-    const float2 mlv = ws_ml[(int64_t)(lv ? sk : s0) * BHq + r];
-    float ov[kMergeChunk][T];
+    for (int tt = 0; tt < T; ++tt) acc[tt] = 0.f;
+    for (int c0 = s0 + wave; c0 < s1; c0 += kMergeChunk * kMergeWaves) {
+      // Lane k < kMergeChunk loads (max, sum) of the chunk's segment k; every lane
+      // loads its channel of each segment's output. Segments past the range load
+      // the first one again and weigh 0.
+      const int sk = c0 + (int)(lane % kMergeChunk) * kMergeWaves;
+      const bool lv = lane < (uint32_t)kMergeChunk && sk < s1;
+      const float2 mlv = ws_ml[(int64_t)(lv ? sk : s0) * BHq + r];
+      float ov[kMergeChunk][T];
 #pragma unroll
-    for (int k = 0; k < kMergeChunk; ++k) {
-      const int s = c0 + k * kMergeWaves < s1 ? c0 + k * kMergeWaves : s0;
-      const float* o = ws_o + ((int64_t)s * BHq + r) * d + lane;
+      for (int k = 0; k < kMergeChunk; ++k) {
+        const int s = c0 + k * kMergeWaves < s1 ? c0 + k * kMergeWaves : s0;
+        const float* o = ws_o + ((int64_t)s * BHq + r) * d + lane;
 #pragma unroll
-      for (int tt = 0; tt < T; ++tt) ov[k][tt] = o[kTile * tt];
+        for (int tt = 0; tt < T; ++tt) ov[k][tt] = o[kTile * tt];
+      }
+      const float xv = lv ? mlv.x : -INFINITY;
+      const float cm = fmaxf(m, wave_max_u(xv));
+      // Rescale the running state to the new maximum (m = -inf gives 0; with no
+      // segment seen yet the state is empty and stays so).
+      const float sr = cm == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - cm);
+      const float wv = xv == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(xv - cm);
+      l = fmaf(l, sr, wave_sum_u(wv * mlv.y));
+#pragma unroll
+      for (int tt = 0; tt < T; ++tt) acc[tt] *= sr;
+#pragma unroll
+      for (int k = 0; k < kMergeChunk; ++k) {
+        const float w = readlane_f(wv, k);
+#pragma unroll
+        for (int tt = 0; tt < T; ++tt) acc[tt] = fmaf(!SELECT || c0 + k * kMergeWaves < s1 ? ov[k][tt] : 0.f, w, acc[tt]);
+      }
+      m = cm;
     }
-    const float xv = lv ? mlv.x : -INFINITY;
-    const float cm = fmaxf(m, wave_max_u(xv));
-    // Rescale the running state to the new maximum (m = -inf gives 0; with no
-    // segment seen yet the state is empty and stays so).
-    const float sr = cm == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - cm);
-    const float wv = xv == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(xv - cm);
-    l = fmaf(l, sr, wave_sum_u(wv * mlv.y));
+  };
+  accumulate(std::false_type{});
+  bool nan = false;
 #pragma unroll
-    for (int tt = 0; tt < T; ++tt) acc[tt] *= sr;
-#pragma unroll
-    for (int k = 0; k < kMergeChunk; ++k) {
-      const float w = readlane_f(wv, k);
-#pragma unroll
-      for (int tt = 0; tt < T; ++tt) acc[tt] = fmaf(ov[k][tt], w, acc[tt]);
-    }
-    m = cm;
-  }
+  for (int tt = 0; tt < T; ++tt) nan |= acc[tt] != acc[tt];
+  if (ballot(nan)) accumulate(std::true_type{});  // (selecting always: 1% of a call on 32 streams of 4K tokens)
   if (lane == 0) {
     wm[wave] = m;
     wl[wave] = l;
