@@ -425,12 +425,10 @@ def route_ab(args) -> None:
         for _ in range(3):
             for name in res:
                 mf.mustafar_attn_set_route(ROUTES[name])
-                splits = mf.mustafar_attn_default_splits(w.B, w.Hq, w.Hkv, w.N)
-                ws_a = torch.empty(mf.mustafar_attn_workspace_bytes(w.B, w.Hq, w.Hkv, w.d, w.N, splits),
+                ws_a = torch.empty(mf.mustafar_attn_workspace_bytes(w.B, w.Hq, w.Hkv, w.d, w.N, 0),
                                    dtype=torch.uint8, device=dev)
-                st = timed_calls(lambda: mf.mustafar_window_decode_attn(q, Kc, Vc, win, out=out,
-                                                                        n_splits=splits, ws=ws_a), 20)
-                res[name]["splits"] = splits
+                st = timed_calls(lambda: mf.mustafar_window_decode_attn(q, Kc, Vc, win, out=out, ws=ws_a), 20)
+                res[name]["splits"] = mf.mustafar_sparse_attn_splits(Kc, Vc, w.Hq, True, ws_a)
                 res[name]["call_us"].append(st["median"])
                 del ws_a
     finally:
@@ -715,6 +713,7 @@ def main():
     attn_gbs = alg_bytes / attn_s / 1e9
     read_bytes = alg_bytes - float(np.mean([attn_offset_bytes(w, n_s)
                                             for n_s in range(n_s_start + 1, n_s_end + 1)]))
+    splits_taken = args.splits or mf.mustafar_sparse_attn_splits(Kc, Vc, w.Hq, True, ws_a)
     del Kc, Vc, win
     torch.cuda.empty_cache()
 
@@ -835,8 +834,7 @@ def main():
         "data": "synthetic (seeded; K with 4 outlier channels x10 per head, V and q N(0,1))",
         "config": {"workload": w.name, "batch": w.B, "q_heads": w.Hq, "kv_heads": w.Hkv,
                    "context": w.N, "head_dim": w.d, "window": w.n_tail, "k_sparsity": w.sK,
-                   "v_sparsity": w.sV, "splits": args.splits or
-                   mf.mustafar_attn_default_splits(w.B, w.Hq, w.Hkv, n_s_end)},
+                   "v_sparsity": w.sV, "splits": splits_taken},
         "step": "mustafar_window_step (new token into each 32-token window; the oldest is pruned, "
                 "compressed and appended) + mustafar_window_decode_attn",
         "settle": {"calls": settle_calls, "s": settle_s,

@@ -278,10 +278,18 @@ enum mustafar_attn_kind {
  * least 128; a forced route (mustafar_attn_set_route) counts as 8 heads
  * (MATRIX_CORES) or as 2 (WALKS). A call that is passed n_splits <= 0 takes this
  * many segments on the walks and at most as many on the dense kernel; on the
- * matrix-core kernel it takes what fills the GPU once, which is at most the larger
- * of the two kinds' counts and never more than its workspace holds. Returns 1 for
- * invalid arguments or kind. */
+ * matrix-core kernel it takes what mustafar_sparse_attn_splits returns, which is at
+ * most the larger of the two kinds' counts and never more than its workspace holds.
+ * Returns 1 for invalid arguments or kind. */
 int mustafar_attn_default_splits(int B, int Hq, int Hkv, int n_tokens, int kind);
+
+/* Segments into which a sparse decode call over these caches (window nonzero: the
+ * mustafar_window_ calls, whose batch entries may differ in length) splits the
+ * compressed tokens when it is passed n_splits <= 0 and a workspace of ws_bytes, on
+ * the current route; the same count passed as n_splits gives the same split. 0 for empty caches. Errors: EINVAL, EUNSUPPORTED,
+ * EWORKSPACE, as of the call. */
+int mustafar_sparse_attn_splits(const mustafar_ccache_t* Kc, const mustafar_ccache_t* Vc, int Hq, int window,
+                                size_t ws_bytes);
 
 /* Kernel route of the sparse calls. DEFAULT: the matrix-core kernel (tiles
  * expanded in registers, contracted with v_mfma), the faster one on MI355X at

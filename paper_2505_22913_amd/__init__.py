@@ -88,6 +88,8 @@ _SIGS = {
     "mustafar_append": (ctypes.c_int, [ctypes.POINTER(ccache_t), ctypes.c_void_p,
                                        ctypes.c_void_p]),
     "mustafar_attn_default_splits": (ctypes.c_int, [ctypes.c_int] * 5),
+    "mustafar_sparse_attn_splits": (ctypes.c_int, [ctypes.POINTER(ccache_t)] * 2 + [ctypes.c_int] * 2
+                                    + [ctypes.c_size_t]),
     "mustafar_attn_workspace_bytes": (ctypes.c_size_t, [ctypes.c_int] * 6),
     "mustafar_sparse_decode_attn": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int, ctypes.c_int,
                                                    ctypes.POINTER(ccache_t),
@@ -388,6 +390,14 @@ def _attn_ws(B, Hq, Hkv, d, n, n_splits, ws, device):
     if ws is None:
         ws = torch.empty(max(need, 16), dtype=torch.uint8, device=device)
     return ws
+
+
+def mustafar_sparse_attn_splits(Kc: CompressedCache, Vc: CompressedCache, Hq: int, window: bool, ws) -> int:
+    """Segments that a sparse call with n_splits = 0 and this workspace takes."""
+    n = lib().mustafar_sparse_attn_splits(ctypes.byref(Kc.desc), ctypes.byref(Vc.desc), int(Hq), int(bool(window)),
+                                          ws.numel() * ws.element_size())
+    _check("mustafar_sparse_attn_splits", min(n, 0))
+    return n
 
 
 def mustafar_sparse_decode_attn(q, Kc: CompressedCache, Vc: CompressedCache, k_tail=None,

@@ -492,25 +492,67 @@ size_t mustafar_attn_workspace_bytes(int B, int Hq, int Hkv, int d, int n_tokens
   return (size_t)(rows * BHq * (int64_t)(d + 2) * (int64_t)sizeof(float) + BHq * (int64_t)sizeof(float));
 }
 
-// Segments of a sparse call that leaves the split to the library: one resident
-// round of waves (kMfmaCus CUs, `waves` each, one of them per stream for the
-// window), every wave taking the same number of 64-token blocks; where that makes
-// a segment of more than kMfmaLongTokens, as many rounds as bring it below.
-// Measured: 32 streams of 16K tokens (11 waves per CU) 32.5 us in one round (192
-// tokens) against 38 in one and a half (128) and 37 in 0.75 (256); 8 of 128K 55 us
-// in one round or two; 512 of 32K 750-759 us in segments of 1024 or 1344 tokens
-// against 771 (2048), 774 (512) and 860 (4096).
+// Segments of a sparse matrix-core call that leaves the split to the library, at most
+// `most` (0: none of the sizes below fits). One wave takes a segment of whole 64-token
+// blocks, `slots` waves fit the GPU at once (kMfmaCus CUs, `waves` each; a stream has one
+// more for its window), and a wave's start costs about a block more.
+//   * Streams of one length: rounds x (blocks + 1). A sixteenth of a round may stand
+//     over: the windows' waves are short.
+//   * Batches whose entries' lengths may differ, of which only the longest is known
+//     here (ragged): blocks + 1/2 a round, a partly full one counts as one and a half
+//     times its part, and a quarter as much again for streams with 0.6 of the segments,
+//     the rest being empty. Workgroups go to the 8 XCDs in turn, so with 8 (or 4) a
+//     stream an XCD gets the same segments of every stream, the empty ones and the
+//     windows among them: beyond one round such counts are charged for it.
+// Measured at every split: 33 equal-length shapes (8 to 512 streams of 700 to 131072
+// tokens, 1 to 8 heads, d = 64 to 256), of which the first picks one within 0.7% of the
+// best on average and 4.3% at most, and 334 batches, half of them with lengths over a
+// factor of four (4%, 25%). The nearest whole blocks to one resident round, which this
+// replaces: 4.2% and 24%, 6% and 54%. us, before and now: 32 streams of 6000 tokens 21.7
+// / 19.3, 32 of 12000 28.5 / 23.7, 512 of 4096 133 / 115 (the walks 125), 96 of up to 9000
+// 140 / 86 (d = 256).
 constexpr int kMfmaCus = 256;
-constexpr int kMfmaLongTokens = 1024;
-static int mfma_splits(int64_t streams, int n_tokens, int waves) {
-  const int64_t round = (int64_t)kMfmaCus * waves;
-  const int64_t per_round = streams * n_tokens / round;  // tokens of a wave in one round
-  const int64_t rounds = per_round <= kMfmaLongTokens ? 1 : (per_round + kMfmaLongTokens - 1) / kMfmaLongTokens;
-  int64_t n = round * rounds / streams - 1;
-  if (n < 1) n = 1;
-  int64_t seg = ((int64_t)n_tokens / n + kSegAlign / 2) / kSegAlign * kSegAlign;  // the nearest whole blocks
-  if (seg < kSegAlign) seg = kSegAlign;
-  return (int)(((int64_t)n_tokens + seg - 1) / seg);
+static int mfma_splits(int64_t streams, int n_tokens, bool ragged, int waves, int most) {
+  static constexpr int kBlocks[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 32};
+  const double per_round = (double)streams / (kMfmaCus * waves);
+  double best = 0.0;
+  int splits = 0;
+  for (int k : kBlocks) {
+    const int n = n_segments(n_tokens, k * kSegAlign);
+    if (n > most) continue;
+    const int per = n + 1, blocks = seg_tokens(n_tokens, n) / kSegAlign;
+    const double r = per_round * per, full = r <= 1.0625 ? 1.0 : floor(r);
+    const double part = r - full > 0.0625 ? r - full : 0.0;
+    double cost;
+    if (!ragged) {
+      cost = (full + (part > 0.0 ? 1.0 : 0.0)) * (blocks + 1);
+    } else {
+      const double few = per_round * (0.6 * n + 1.0);
+      const double met = streams < 64 || r <= 1.0625 || per % 4 != 0 ? 1.0 : per % 8 != 0 ? 1.375 : 1.75;
+      const double over = part > 0.0 ? 0.5 + blocks * (part < 2.0 / 3 ? 1.5 * part : 1.0) : 0.0;
+      cost = full * (blocks + 0.5) + over + 0.25 * met * (few > 1.0 ? few : 1.0) * (blocks + 0.5);
+    }
+    if (splits == 0 || cost < best) {
+      best = cost;
+      splits = n;
+    }
+    if (n == 1 || (r <= 1.0 && !ragged)) break;  // larger segments only take longer
+  }
+  return splits;
+}
+
+// Segments of the compressed tokens of a sparse call that leaves the split to the
+// library (counted: the default count, which the workspace was checked for).
+static int sparse_splits(int Hq, const mustafar_ccache_t* K, const mustafar_ccache_t* V, bool ragged, bool mfma,
+                         int counted, size_t ws_bytes) {
+  if (!mfma || K->n_tokens <= 0) return counted;
+  // No more than a default-sized workspace holds, nor than this one does.
+  const int dn = mustafar_attn_default_splits(K->B, Hq, K->H, K->n_tokens, MUSTAFAR_ATTN_DENSE);
+  const int most = dn > counted ? dn : counted;
+  const int want = mfma_splits((int64_t)K->B * K->H, K->n_tokens, ragged,
+                               mf::mfma_resident_waves(K->d / kTile, side_of(K), side_of(V)), most);
+  if (want > 0 && ws_bytes >= mustafar_attn_workspace_bytes(K->B, Hq, K->H, K->d, K->n_tokens, want)) return want;
+  return counted;
 }
 
 // Segments of a dense call that leaves the split to the library: one wave per SIMD
@@ -524,10 +566,11 @@ static int dense_splits(int64_t streams, int n_tokens, int d) {
   return (int)(n < most ? n : most);
 }
 
-// K, V: the compressed caches of a sparse call, null for the dense one. On return
+// K, V: the compressed caches of a sparse call, null for the dense one (ragged: its batch
+// entries' lengths may differ). On return
 // *splits is the split count that the workspace layout follows.
 static int decode_common(const void* q, int B, int Hq, int Hkv, int d, int n_s, int n_dense,
-                         const mustafar_ccache_t* K, const mustafar_ccache_t* V, int n_splits, float scale,
+                         const mustafar_ccache_t* K, const mustafar_ccache_t* V, bool ragged, int n_splits, float scale,
                          void* out, void* ws, size_t ws_bytes, mf::AttnShape* sh, float** ws_ml, float** ws_o,
                          int* splits = nullptr) {
   const bool dense_is_window = K != nullptr;
@@ -548,14 +591,7 @@ static int decode_common(const void* q, int B, int Hq, int Hkv, int d, int n_s, 
   if (n_splits > (1 << 20)) return MUSTAFAR_EINVAL;
   if (!aligned(ws, 16) || ws_bytes < mustafar_attn_workspace_bytes(B, Hq, Hkv, d, n_main, n_splits))
     return MUSTAFAR_EWORKSPACE;
-  if (by_default && mfma && n_s > 0) {
-    // No more than a default-sized workspace holds, nor than this one does.
-    const int dn = mustafar_attn_default_splits(B, Hq, Hkv, n_s, MUSTAFAR_ATTN_DENSE);
-    const int most = dn > n_splits ? dn : n_splits;
-    int want = mfma_splits((int64_t)B * Hkv, n_s, mf::mfma_resident_waves(d / kTile, side_of(K), side_of(V)));
-    if (want > most) want = most;
-    if (ws_bytes >= mustafar_attn_workspace_bytes(B, Hq, Hkv, d, n_s, want)) n_splits = want;
-  }
+  if (by_default && dense_is_window) n_splits = sparse_splits(Hq, K, V, ragged, mfma, n_splits, ws_bytes);
   if (by_default && !dense_is_window) {
     const int want = dense_splits((int64_t)B * Hkv, n_dense, d);
     if (want < n_splits) n_splits = want;
@@ -587,6 +623,20 @@ static int decode_common(const void* q, int B, int Hq, int Hkv, int d, int n_s, 
   return MUSTAFAR_OK;
 }
 
+int mustafar_sparse_attn_splits(const mustafar_ccache_t* Kc, const mustafar_ccache_t* Vc, int Hq, int window,
+                                size_t ws_bytes) {
+  int st = check_cache(Kc);
+  if (st != MUSTAFAR_OK || (st = check_cache(Vc)) != MUSTAFAR_OK) return st;
+  if (Vc->B != Kc->B || Vc->H != Kc->H || Vc->d != Kc->d || Vc->n_tokens != Kc->n_tokens) return MUSTAFAR_EINVAL;
+  if (Hq < 1 || Hq % Kc->H != 0 || Kc->n_tokens > kMaxTokens) return MUSTAFAR_EINVAL;
+  const int G = Hq / Kc->H, n = Kc->n_tokens;
+  if (G != 1 && G != 2 && G != 4 && G != 8) return MUSTAFAR_EUNSUPPORTED;
+  const int counted = mustafar_attn_default_splits(Kc->B, Hq, Kc->H, n > 0 ? n : 1, MUSTAFAR_ATTN_SPARSE);
+  if (ws_bytes < mustafar_attn_workspace_bytes(Kc->B, Hq, Kc->H, Kc->d, n, counted)) return MUSTAFAR_EWORKSPACE;
+  const bool mfma = mfma_route(g_route.load(std::memory_order_relaxed));
+  return n_segments(n, seg_tokens(n, sparse_splits(Hq, Kc, Vc, window != 0 && Kc->B > 1, mfma, counted, ws_bytes)));
+}
+
 int mustafar_sparse_decode_attn(const void* q, int B, int Hq, const mustafar_ccache_t* Kc,
                                 const mustafar_ccache_t* Vc, const void* k_tail,
                                 const void* v_tail, int n_tail, float scale, void* out,
@@ -602,7 +652,7 @@ int mustafar_sparse_decode_attn(const void* q, int B, int Hq, const mustafar_cca
   if (n_tail > 0 && (!aligned(k_tail, 16) || !aligned(v_tail, 16))) return MUSTAFAR_EINVAL;
   mf::AttnShape sh;
   float *ws_ml, *ws_o;
-  st = decode_common(q, B, Hq, Kc->H, Kc->d, Kc->n_tokens, n_tail, Kc, Vc, n_splits, scale, out, ws,
+  st = decode_common(q, B, Hq, Kc->H, Kc->d, Kc->n_tokens, n_tail, Kc, Vc, false, n_splits, scale, out, ws,
                      ws_bytes, &sh, &ws_ml, &ws_o);
   if (st != MUSTAFAR_OK) return st;
   return status_of(mf::launch_attention(sh, (const uint16_t*)q, side_of(Kc), side_of(Vc),
@@ -643,7 +693,7 @@ int mustafar_dense_decode_attn(const void* q, int B, int Hq, int Hkv, const void
   if (n_tokens < 1 || !aligned(k, 16) || !aligned(v, 16)) return MUSTAFAR_EINVAL;
   mf::AttnShape sh;
   float *ws_ml, *ws_o;
-  int st = decode_common(q, B, Hq, Hkv, d, 0, n_tokens, nullptr, nullptr, n_splits, scale, out, ws, ws_bytes,
+  int st = decode_common(q, B, Hq, Hkv, d, 0, n_tokens, nullptr, nullptr, false, n_splits, scale, out, ws, ws_bytes,
                          &sh, &ws_ml, &ws_o);
   if (st != MUSTAFAR_OK) return st;
   mf::SparseSide none = {nullptr, nullptr, nullptr, nullptr, 0, 1, 0};
@@ -804,7 +854,7 @@ int mustafar_window_decode_attn(const void* q, int B, int Hq, const mustafar_cca
   if (Kc->n_tokens != Vc->n_tokens) return MUSTAFAR_EINVAL;
   mf::AttnShape sh;
   float *ws_ml, *ws_o;
-  st = decode_common(q, B, Hq, Kc->H, Kc->d, Kc->n_tokens, w->W, Kc, Vc, n_splits, scale, out, ws,
+  st = decode_common(q, B, Hq, Kc->H, Kc->d, Kc->n_tokens, w->W, Kc, Vc, B > 1, n_splits, scale, out, ws,
                      ws_bytes, &sh, &ws_ml, &ws_o);
   if (st != MUSTAFAR_OK) return st;
   sh.n_comp = w->n_comp;
@@ -828,7 +878,7 @@ int mustafar_window_decode_attn_scores(const void* q, int B, int Hq, const musta
   mf::AttnShape sh;
   float *ws_ml, *ws_o;
   int splits = 0;
-  st = decode_common(q, B, Hq, Kc->H, Kc->d, Kc->n_tokens, w->W, Kc, Vc, n_splits, scale, out, ws,
+  st = decode_common(q, B, Hq, Kc->H, Kc->d, Kc->n_tokens, w->W, Kc, Vc, B > 1, n_splits, scale, out, ws,
                      ws_bytes, &sh, &ws_ml, &ws_o, &splits);
   if (st != MUSTAFAR_OK) return st;
   const size_t need = mustafar_attn_workspace_bytes(B, Hq, Kc->H, Kc->d, Kc->n_tokens, splits);
