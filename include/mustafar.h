@@ -176,9 +176,9 @@ int mustafar_prune_compress(mustafar_ccache_t* c, const void* x, int n_new, void
 /* mustafar_prune_compress with the caller's bound on the look-back of a chunk,
  * counted in reads of the other chunks' totals (for callers with a latency
  * budget, and to exercise the give-up path: with max_polls = 0 no chunk but the
- * first of a stream may read, so every stream of more than one chunk -- 64
- * tokens, 128 at d = 64 -- is poisoned). Same arguments, status word and
- * errors. */
+ * first of a stream may read, so every stream of more than one chunk is
+ * poisoned; the chunks are those of mustafar_prune_compress, 64 to 1024 tokens by
+ * head size, streams and tokens). Same arguments, status word and errors. */
 int mustafar_prune_compress_bounded(mustafar_ccache_t* c, const void* x, int n_new, uint32_t max_polls,
                                     void* ws, size_t ws_bytes, void* stream);
 

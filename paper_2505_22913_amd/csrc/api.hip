@@ -326,7 +326,7 @@ size_t mustafar_compress_workspace_bytes(int B, int H, int n_new) {
   if ((int64_t)B * H > kMaxGrid) return 0;  // no compression call accepts more streams
   const int64_t n_chunks = ((int64_t)n_new + mf::kMinCompressChunk - 1) / mf::kMinCompressChunk;
   // the status word (16 bytes), then per stream a look-back flag per chunk, a
-  // ticket counter and a give-up mark
+  // ticket counter and a count of decided chunks (with the give-up mark)
   return (size_t)(16 + (int64_t)B * H * (n_chunks * (int64_t)sizeof(uint64_t) + 2 * (int64_t)sizeof(uint32_t)));
 }
 
@@ -744,20 +744,27 @@ int mustafar_window_prefill(mustafar_window_t* w, mustafar_ccache_t* Kc, mustafa
     return MUSTAFAR_EWORKSPACE;
   const hipStream_t s = (hipStream_t)stream;
   const int64_t entry = (int64_t)w->H * n_max * w->d;  // fp16 elements per batch entry of x
-  // As many entries at a time as the workspace has look-back flags for: one call's
-  // worth for a single entry is enough for several, as a chunk of many streams is
-  // longer than the one it is sized by. (One entry at a time took 4 to 6 launches
-  // each: 48 for 8 entries, of 4 to 9 us.)
+  // As many entries at a time as the workspace has look-back flags for, in wider chunks
+  // than they would take if that makes them fit: one call's worth for a single entry is
+  // enough for several, as a chunk is longer than the one it is sized by. (One entry at a time took 4 to 6 launches each: 48 for 8 entries, of 4
+  // to 9 us.)
   for (int b0 = 0; b0 < w->B;) {
-    int n = w->B - b0 < mf::kMaxPruneHeads ? w->B - b0 : mf::kMaxPruneHeads;
-    while (max_comp > 0 && n > 1 && mf::compress_ws_bytes(w->d / kTile, (int64_t)n * w->H, n_max) > ws_bytes) n = (n + 1) / 2;
     int32_t comp[mf::kMaxPruneHeads], len[mf::kMaxPruneHeads];
-    int most_comp = 0, most_len = 0;
-    for (int e = 0; e < n; ++e) {
-      len[e] = prefill_window_len(w, Vc, seq_len[b0 + e]);
-      comp[e] = seq_len[b0 + e] - len[e];
-      if (comp[e] > most_comp) most_comp = comp[e];
-      if (len[e] > most_len) most_len = len[e];
+    int most_comp = 0, most_len = 0, waves = 0, n = w->B - b0 < mf::kMaxPruneHeads ? w->B - b0 : mf::kMaxPruneHeads;
+    for (;; n = (n + 1) / 2) {
+      most_comp = most_len = 0;
+      for (int e = 0; e < n; ++e) {
+        len[e] = prefill_window_len(w, Vc, seq_len[b0 + e]);
+        comp[e] = seq_len[b0 + e] - len[e];
+        if (comp[e] > most_comp) most_comp = comp[e];
+        if (len[e] > most_len) most_len = len[e];
+      }
+      const int T = w->d / kTile;
+      const int64_t streams = (int64_t)n * w->H;
+      waves = mf::compress_waves(T, streams, most_comp);
+      if (n == 1 || most_comp == 0) break;
+      while (waves < mf::widest_compress(T) && mf::compress_ws_bytes(T, streams, most_comp, waves) > ws_bytes) waves *= 2;
+      if (mf::compress_ws_bytes(T, streams, most_comp, waves) <= ws_bytes) break;
     }
     const uint16_t* xk = (const uint16_t*)x_k + b0 * entry;
     const uint16_t* xv = (const uint16_t*)x_v + b0 * entry;
@@ -766,6 +773,7 @@ int mustafar_window_prefill(mustafar_window_t* w, mustafar_ccache_t* Kc, mustafa
       mf::CacheView kv = view_of(&kb), vv = view_of(&vb);
       kv.entry_streams = vv.entry_streams = w->H;
       kv.entry_tokens = vv.entry_tokens = comp;
+      kv.waves = vv.waves = waves;
       if ((st = status_of(grouped(Vc) ? mf::launch_compress_channel(vv, xv, most_comp, 0, (uint32_t*)ws, s, nullptr, n_max)
                                       : mf::launch_compress(vv, xv, most_comp, 0, (uint32_t*)ws, s, n_max))) !=
               MUSTAFAR_OK ||

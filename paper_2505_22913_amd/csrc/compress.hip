@@ -1332,9 +1332,9 @@ template <int T, int MODE>
 static hipError_t compress_launch(const CacheView& c, const uint16_t* x, int n_new, int64_t x_stride,
                                   int tok0, uint32_t* ws, hipStream_t s, const PruneOpts& o,
                                   uint32_t max_polls) {
-  constexpr int kWide = T == 4 ? 4 : 8;
-  // (the variants have one width: the scored selection's registers)
-  const int W = MODE >= kScored ? kWide : compress_waves(T, c.BH, max_polls != kLookbackPolls);
+  const int W = c.waves > 0        ? c.waves
+                : MODE >= kScored ? compress_waves_selected(T, c.BH, n_new)
+                                  : compress_waves(T, c.BH, n_new);
   const int chunk = compress_chunk_tokens(T) / 2 * W;
   const int n_chunks = (n_new + chunk - 1) / chunk;
   const int64_t n_wg = (int64_t)c.BH * n_chunks;
@@ -1348,7 +1348,9 @@ static hipError_t compress_launch(const CacheView& c, const uint16_t* x, int n_n
                        c.bitmaps, c.offsets, c.values, c.stream_len, c.cap_tokens, tok0, c.val_stride,
                        w.flags, w.ticket, n_chunks, x_stride, o, max_polls, w.decided, w.status);
   };
-  if (W == kWide) launch(k_compress<T, MODE, kWide>, kWide);
+  if (W == 4) launch(k_compress<T, MODE, 4>, 4);
+  if constexpr (T <= 2)
+    if (W == 8) launch(k_compress<T, MODE, 8>, 8);
   if constexpr (MODE < kScored) {
     if (W == 2) launch(k_compress<T, MODE, 2>, 2);
     if constexpr (T <= 2)

@@ -28,20 +28,33 @@ struct CacheView {
   // kMaxPruneHeads entries); n_new is then the largest of them.
   int entry_streams = 0;
   const int32_t* entry_tokens = nullptr;
+  int waves = 0;     // their waves per workgroup (0: compress_waves)
 };
 
-// Waves per workgroup of the bulk compression of BH streams, i.e. its chunk. A
-// chunk's base needs the totals of all chunks before it, and few streams have
-// many chunks of each in flight that wait for one another: with two waves, 32
-// streams of 16K tokens at d = 128 (50%) took 110 us against 60 with eight, 8 of
-// 128K 295 against 163 (139 with 16, which leaves one workgroup a CU and costs
-// 10-20% from 32 streams on), 128 of 16K 217 against 172, 256 of 16K 356 against 348.
-// 512 streams have few chunks of each in flight, and two waves leave more workgroups
-// a CU: 4K tokens each 186 against 198 with eight, d = 64 of 8K 171 against 188. d = 256: four (60 against 76; eight 68). A caller's bound on
-// the look-back counts chunks of two waves.
+// Waves per workgroup of the bulk compression of n_new tokens in each of BH streams,
+// i.e. its chunk. A chunk's base needs the totals of all chunks before it, and few
+// streams have many chunks of each in flight that wait for one another, so they take
+// wide chunks; short calls have no queue and take less LDS and fewer idle waves, and from
+// 512 streams on two waves leave more workgroups a CU. us, in 2 / 4 / 8 / 16 waves (d =
+// 128, 50%): 4 streams of 100 tokens 9.8 / 9.0 / 10.0 / 12.2, 8 of 2048 13.3 / 11.7 / 12.4
+// / 14.7, 8 of 16K 50 / 34 / 24 / 21, 32 of 2048 21.9 / 16.2 / 14.7 / 16.8, 32 of 16K 109 /
+// 75 / 62 / 68, 96 of 4096 56 / 43 / 42, 128 of 16K 217 / 180 / 185, 256 of 4096 97 / 93 /
+// 98 / 120, 512 of 1024 48.7 / 50.6 / 52 / 66; d = 64, 256 of 4096 50 / 47 / 53 / 72; d = 256,
+// 32 of 8192 79 / 63 / 70, 128 of 2048 59 / 55 / 69.
 constexpr int64_t kManyStreams = 512;
-constexpr int compress_waves(int T, int64_t BH, bool bounded) {
-  return bounded || BH >= kManyStreams ? 2 : T == 4 ? 4 : BH <= 16 ? 16 : 8;
+constexpr int compress_waves(int T, int64_t BH, int64_t n_new) {
+  if (BH >= kManyStreams) return 2;
+  const int64_t tokens = compress_chunk_tokens(T) / 2, waves = BH * ((n_new + tokens - 1) / tokens);
+  if (T == 4 || BH >= 128 || waves < 2048) return 4;
+  return BH <= 16 && waves >= 4096 ? 16 : 8;
+}
+constexpr int widest_compress(int T) { return T == 4 ? 4 : 16; }
+// The same for the scored and 2:4 selections, in 4 / 8 waves (d = 128): scored 8 streams of
+// 16K 48 / 39, 32 of 16K 118 / 127, 128 of 4096 98 / 125, 512 of 1024 99 / 124 (102 in two); 2:4
+// 8 of 16K 34 / 26, 32 of 16K 68.6 / 69.3, 128 of 4096 58 / 64, 512 of 1024 57 / 63 (54 in
+// two). d = 256, scored, 32 of 2048 37 / 42.
+constexpr int compress_waves_selected(int T, int64_t BH, int64_t n_new) {
+  return compress_waves(T, BH, n_new) == 16 ? 8 : 4;
 }
 
 // A stream whose bulk compression gave up waiting in the look-back (see
@@ -73,8 +86,8 @@ inline CompressWs compress_ws(uint32_t* ws, int64_t BH, int64_t n_chunks) {
   return w;
 }
 
-inline size_t compress_ws_bytes(int T, int64_t BH, int64_t n_new) {
-  const int64_t chunk = compress_chunk_tokens(T) / 2 * compress_waves(T, BH, false);
+inline size_t compress_ws_bytes(int T, int64_t BH, int64_t n_new, int waves) {
+  const int64_t chunk = compress_chunk_tokens(T) / 2 * waves;
   return 4u * (size_t)compress_ws_words(BH, (n_new + chunk - 1) / chunk);
 }
 

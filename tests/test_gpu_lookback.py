@@ -73,3 +73,35 @@ def test_one_chunk_needs_no_look_back(d):
     mf.mustafar_prune_compress_bounded(Kc, to_dev(K), 0, ws=ws)
     assert mf.compress_status(ws) == 0
     compare_format(read_cache(Kc), oracle.compress(K, 0.5), N, all_pairs(B, H))
+
+
+@pytest.mark.parametrize("d,B,H,n,chunk", [
+    (128, 1, 4, 129, 128), (128, 2, 16, 2048, 256), (128, 1, 8, 16384, 512), (128, 16, 32, 65, 64),
+    (64, 1, 4, 257, 256), (64, 2, 16, 4096, 512), (64, 1, 16, 16384, 1024), (64, 16, 32, 129, 128),
+    (256, 1, 4, 129, 128), (256, 16, 32, 65, 64)])
+@pytest.mark.parametrize("grouped", [False, True])
+def test_give_up_at_every_chunk_width(d, B, H, n, chunk, grouped):
+    # 2, 4, 8 and 16 waves a chunk: with bound 0 a stream's first chunk alone is written
+    # and every stream is poisoned; refilled with the default bound it is whole.
+    import torch
+    n = (n + 31) // 32 * 32 if grouped else n
+    announce(f"look-back bound 0 d={d} {B}x{H} streams n={n} grouped={grouped}")
+    X, _ = synth.make_kv(B, H, n, d, seed=93)
+    x = to_dev(X)
+    c = mf.CompressedCache(B, H, d, 0.5, n, grouped=grouped)
+    ws = torch.empty(mf.mustafar_compress_workspace_bytes(B, H, n), dtype=torch.uint8, device="cuda")
+    mf.mustafar_prune_compress_bounded(c, x, 0, ws=ws)
+    assert mf.compress_status(ws) != 0
+    got = read_cache(c)
+    want = oracle.compress_grouped(X, 0.5) if grouped else oracle.compress(X, 0.5, threads=4)
+    assert (got["stream_len"] == mf.STREAM_POISONED).all()
+    assert np.array_equal(got["offsets"][:, :, :chunk], want["offsets"][:, :, :chunk])
+    assert not got["offsets"][:, :, chunk:].any()
+    for b, h in ((0, 0), (B - 1, H - 1)):
+        end = int(want["offsets"][b, h, chunk, 0])
+        assert np.array_equal(got["values"][b, h, :end], want["values"][b, h, :end])
+        assert not got["values"][b, h, end:].any()
+    c.desc.n_tokens = 0
+    mf.mustafar_prune_compress(c, x, ws=ws)
+    assert mf.compress_status(ws) == 0
+    compare_format(read_cache(c), want, n, all_pairs(B, H))
