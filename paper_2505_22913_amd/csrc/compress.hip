@@ -678,7 +678,8 @@ __global__ __launch_bounds__(W * kWave) void k_compress(const uint16_t* __restri
 
 // Output-aware keep-mask of one token, lane = channel: the score |x| * w in
 // fp32 (one rounding) of channel 64 t + lane, w the token's fp32 channel
-// weights; non-negative, so its bits order like its value (31 significant bits).
+// weights; non-negative, so its 31 bits order like its value (the sign of a weight
+// of -0.0 left out, as k_compress does).
 template <int T>
 __device__ __forceinline__ void select_output_aware(int k, const uint16_t (&xv)[T],
                                                     const float* __restrict__ w, uint32_t lane,
@@ -687,7 +688,7 @@ __device__ __forceinline__ void select_output_aware(int k, const uint16_t (&xv)[
 #pragma unroll
   for (int t = 0; t < T; ++t) {
     const float m = fabsf(half_bits_to_float(xv[t]));
-    key[t] = __builtin_bit_cast(uint32_t, m * w[kTile * t + lane]);
+    key[t] = __builtin_bit_cast(uint32_t, m * w[kTile * t + lane]) & 0x7fffffffu;
   }
   select_token<T, 31>(key, k, bm);
 }

@@ -61,6 +61,27 @@ def test_scored_weights_at_any_float(d, skip):
 
 
 @pytest.mark.parametrize("d", [64, 128, 256])
+def test_negative_zero_weights(d):
+    # A weight of -0.0 is a zero: bulk and append agree with the oracle.
+    import torch
+    B, H, n, s = 1, 2, 40, 0.7
+    announce(f"scored, weights of -0.0, d={d}")
+    x, w = _inputs(np.random.default_rng(d + 9), B, H, n, d)
+    w[..., 3::4] = np.float32(-0.0)
+    w[:, :, 5] = np.float32(-0.0)
+    w[:, :, 6, : d // 2] = np.float32(-0.0)
+    wd = torch.from_numpy(w).cuda()
+    want = oracle.compress_variant(x, "output_aware", k=oracle.keep_count(d, s), weights=w)
+    Kc, Ka = mf.CompressedCache(B, H, d, s, n), mf.CompressedCache(B, H, d, s, n)
+    mf.mustafar_prune_compress_ex(Kc, to_dev(x), mode=mf.PRUNE_OUTPUT_AWARE, weights=wd)
+    for i in range(n):
+        mf.mustafar_append_ex(Ka, to_dev(np.ascontiguousarray(x[:, :, i])), mode=mf.PRUNE_OUTPUT_AWARE,
+                              weights=wd[:, :, i].contiguous())
+    compare_format(read_cache(Kc), want, n, all_pairs(B, H))
+    compare_format(read_cache(Ka), want, n, all_pairs(B, H))
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
 def test_scored_counts_per_head(d):
     import torch
     B, H, n = 2, 4, 130
