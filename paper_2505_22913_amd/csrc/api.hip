@@ -784,7 +784,7 @@ int mustafar_window_prefill(mustafar_window_t* w, mustafar_ccache_t* Kc, mustafa
     wv.fill_entries = n;
     wv.fill_first = comp;
     wv.fill_count = len;
-    if ((st = status_of(mf::launch_window_fill(wv, b0, w->d, xk, xv, n_max, most_comp, most_len, s))) != MUSTAFAR_OK)
+    if ((st = status_of(mf::launch_window_fill(wv, b0, w->d, xk, xv, n_max, most_len, s))) != MUSTAFAR_OK)
       return st;
     b0 += n;
   }

@@ -1534,13 +1534,12 @@ hipError_t launch_query_lookahead(const uint16_t* q, int B, int Hq, int Hkv, int
 }
 
 hipError_t launch_window_fill(const WindowView& w, int b, int d, const uint16_t* xk,
-                              const uint16_t* xv, int64_t x_stride, int first, int count,
-                              hipStream_t s) {
-  const int entries = w.fill_entries > 0 ? w.fill_entries : 1;
+                              const uint16_t* xv, int64_t x_stride, int count, hipStream_t s) {
+  const int entries = w.fill_entries;
   FillSpans spans;
   for (int e = 0; e < entries; ++e) {
-    spans.first[e] = w.fill_entries > 0 ? w.fill_first[e] : first;
-    spans.count[e] = w.fill_entries > 0 ? w.fill_count[e] : count;
+    spans.first[e] = w.fill_first[e];
+    spans.count[e] = w.fill_count[e];
   }
   const int64_t n = (int64_t)w.H * count * d / 8;
   int blocks = (int)((n + 255) / 256);

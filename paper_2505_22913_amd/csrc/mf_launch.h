@@ -149,8 +149,7 @@ struct WindowView {
   const int32_t* fill_count = nullptr;
 };
 hipError_t launch_window_fill(const WindowView& w, int b, int d, const uint16_t* xk,
-                              const uint16_t* xv, int64_t x_stride, int first, int count,
-                              hipStream_t s);
+                              const uint16_t* xv, int64_t x_stride, int count, hipStream_t s);
 // kacc: null for magnitude keys, else the window's output-aware key weights
 // [BH][W][64T] fp32 (the leaving key is pruned with its slot's weights).
 hipError_t launch_window_step(const CacheView& kc, const CacheView& vc, const WindowView& w,

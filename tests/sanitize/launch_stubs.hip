@@ -27,7 +27,7 @@ hipError_t launch_query_lookahead(const uint16_t*, int, int, int, int, int, int,
   return ok();
 }
 hipError_t launch_window_fill(const WindowView&, int, int, const uint16_t*, const uint16_t*, int64_t, int,
-                              int, hipStream_t) { return ok(); }
+                              hipStream_t) { return ok(); }
 hipError_t launch_window_step(const CacheView&, const CacheView&, const WindowView&, const uint16_t*,
                               const uint16_t*, const int32_t*, hipStream_t, float*) { return ok(); }
 hipError_t launch_window_key_weights(const WindowView&, const uint16_t*, int, int, const int32_t*, float*,
