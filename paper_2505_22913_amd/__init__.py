@@ -207,7 +207,10 @@ def _stream(stream) -> int | None:
     if stream is not None:
         return stream.cuda_stream
     import torch
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # not public: another torch may lack it
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 # ---- host-only helpers --------------------------------------------------------------------
