@@ -572,7 +572,7 @@ ROUTE_DEFAULT, ROUTE_WALKS, ROUTE_MATRIX_CORES = 0, 1, 2
 
 
 def mustafar_attn_set_route(route: int) -> None:
-    """Kernel route of grouped-query sparse calls (ROUTE_DEFAULT, ROUTE_WALKS, ROUTE_MATRIX_CORES)."""
+    """Kernel route of the sparse calls (ROUTE_DEFAULT, ROUTE_WALKS, ROUTE_MATRIX_CORES)."""
     _check("mustafar_attn_set_route", lib().mustafar_attn_set_route(int(route)))
 
 
