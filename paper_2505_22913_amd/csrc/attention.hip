@@ -755,13 +755,17 @@ __global__ __launch_bounds__(64) void k_sparse_attn(AttnArgs a) {
 // token r, channels 32 c + 8 q), the scores in their result layout (lane = head r,
 // tokens 4 q + e) the A operand of the second product, and lane (q, r) loads channels
 // 4 T r .. of eight tokens and transposes them with byte permutes into its B operand.
-// The probabilities stay what they were in fp32: each enters as two fp16 parts
-// (value and remainder, 21 bits), the sum takes the fp32 one. About 200 vector
-// instructions for 16 KB, so the loads bound it; the kernel before it read V two
-// bytes a lane and did every product on the vector units. Cold, us, before and now:
-// 32 streams of 16K tokens, 4 heads per kv-head, d = 128 68 -> 45 (6.0 TB/s), 8
-// heads 79 -> 46; 128 of 16K, one head 190 -> 154 (7.0 TB/s); d = 64, 2 heads 33 ->
-// 26. Error against 64 bits the same (2.1e-4, the fp16 output's rounding).
+// The probabilities are computed in fp32 and enter as two fp16 parts, the first rounded
+// towards zero: 21 bits of one within 2^-13 of the largest or more, fewer below, and at
+// least 2^-38 of the largest; the sum takes the fp32 one. Against 64 bits the fp32
+// outputs (before the rounding to fp16, 2e-4) are off by 0.5e-7 to 1.1e-6 over 9 shapes of
+// 600 to 65536 tokens in 16 segments; with fp32 probabilities on the vector units it was
+// 0.5e-7 to 1.4e-6, and a third part (24 bits) changes nothing and takes 1-5% longer: the
+// order of the sums decides.
+// About 200 vector instructions for 16 KB, so the loads bound it; the kernel before it
+// read V two bytes a lane and did every product on the vector units. Cold, us, before and
+// now: 32 streams of 16K tokens, 4 heads per kv-head, d = 128 68 -> 45 (6.0 TB/s), 8
+// heads 79 -> 46; 128 of 16K, one head 190 -> 154 (7.0 TB/s); d = 64, 2 heads 33 -> 26.
 // Grid (n_dense_segs, BHkv).
 // ------------------------------------------------------------------------------------------
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
@@ -772,7 +776,8 @@ constexpr float kDensePUnit = 0x1p-15f;  // against the unscaled maximum, as in 
 // The least part of a probability, fp16's least subnormal, 2^-39 of the largest. The
 // first part is rounded towards zero, so both parts are positive and an infinite
 // value (a cache that overflowed) stays infinite: a zero or negative part would turn it
-// into NaN.
+// into NaN. It raises probabilities below 2^-38 of the largest to that: over N tokens the
+// weight it adds is less than N 2^-38 of the largest.
 constexpr float kDenseLeast = 0x1p-24f;
 
 __device__ __forceinline__ half8_t dense_h8(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {

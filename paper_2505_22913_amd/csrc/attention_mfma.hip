@@ -27,7 +27,7 @@
 // and, below about 6 blocks a wave, the latency of one block (1.5 us alone). 32
 // streams of 16K tokens (70/70, warm): 30.6 us with 4 heads (walks 46.9) and 32.1
 // with 8 (57.7 before), 3.7 TB/s of needed bytes with 4 heads (2.4); 512 streams of 32K at
-// K 50% / V 70%: 760 us (822), 5.85 TB/s. Tried and left out: half the key columns
+// K 50% / V 70%: 750 us (822), 5.95 TB/s. Tried and left out: half the key columns
 // at a time (12 waves a CU instead of 9 or 11: +10%), values in 8-byte loads
 // (conflict-free LDS writes: even, +7% at 50%), the metadata loaded before the
 // stream's count is known (even).

@@ -300,9 +300,9 @@ __device__ __forceinline__ void lds_barrier() {
 // kScored: output-aware selection, the same bit-sliced search over the 31 bits of
 // the fp32 scores |x| w (o.weights). What bounds that mode is the reading of the
 // weights (twice the bytes of the tokens): 32 streams of 16K tokens at d = 128
-// (70%) take 119 us, where a kernel that counted the ballots of one token a wave
+// (70%) take 117 us, where a kernel that counted the ballots of one token a wave
 // (250 scalar instructions a token) and the packing after it took 258. MODE
-// kTwoFour: the two largest of every four channels; 66 us at 50% (146 with the ballots).
+// kTwoFour: the two largest of every four channels; 68 us at 50% (146 with the ballots).
 enum { kMagnitude = 0, kPreset = 1, kScored = 2, kTwoFour = 3 };
 template <int T, int MODE, int W>
 __global__ __launch_bounds__(W * kWave) void k_compress(const uint16_t* __restrict__ x, int n_new, int k_all,
