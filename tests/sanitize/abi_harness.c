@@ -105,6 +105,12 @@ int main(void) {
 
     /* decode attention */
     K.n_tokens = V.n_tokens = 64;
+    for (int w = 0; w <= 1; ++w) {
+        EXPECT(mustafar_sparse_attn_splits(&K, &V, 4, w, 0), MUSTAFAR_EWORKSPACE);
+        EXPECT(mustafar_sparse_attn_splits(&K, &V, 4, w, SIZE_MAX), 1);
+        EXPECT(mustafar_sparse_attn_splits(&K, &V, INT_MAX, w, SIZE_MAX), MUSTAFAR_EINVAL);
+        EXPECT(mustafar_sparse_attn_splits(&K, NULL, 4, w, SIZE_MAX), MUSTAFAR_EINVAL);
+    }
     const size_t awb = mustafar_attn_workspace_bytes(2, 16, 4, 128, 64, 0);
     EXPECT(mustafar_sparse_decode_attn(P(0x500000), 2, 16, &K, &V, P(0x900000), P(0x980000), 32, 0.f,
                                        P(0x800000), 0, P(0xa00000), awb, NULL), MUSTAFAR_OK);

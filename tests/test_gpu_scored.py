@@ -104,3 +104,21 @@ def test_two_four_ties_bit_exact(d, B, H):
         Kc = mf.CompressedCache(B, H, d, 0.5, n)
         mf.mustafar_prune_compress_ex(Kc, to_dev(x), mode=mf.PRUNE_2_4)
         compare_format(read_cache(Kc), oracle.compress_variant(x, "2:4"), n, all_pairs(B, H))
+
+
+@pytest.mark.parametrize("mode", ["output_aware", "2:4"])
+@pytest.mark.parametrize("d,n", [(128, 8225), (64, 16449)])
+def test_long_streams_take_wide_chunks(d, n, mode):
+    # 16 streams of 4096 waves of tokens and more: 8 waves a chunk (the other tests: 4).
+    import torch
+    B, H = 1, 16
+    announce(f"{mode} selection in wide chunks d={d} n={n}")
+    x, w = _inputs(np.random.default_rng(d), B, H, n, d)
+    Kc = mf.CompressedCache(B, H, d, 0.5, n)
+    if mode == "2:4":
+        mf.mustafar_prune_compress_ex(Kc, to_dev(x), mode=mf.PRUNE_2_4)
+        want = oracle.compress_variant(x, "2:4")
+    else:
+        mf.mustafar_prune_compress_ex(Kc, to_dev(x), mode=mf.PRUNE_OUTPUT_AWARE, weights=torch.from_numpy(w).cuda())
+        want = oracle.compress_variant(x, "output_aware", k=d // 2, weights=w)
+    compare_format(read_cache(Kc), want, n, all_pairs(B, H))
